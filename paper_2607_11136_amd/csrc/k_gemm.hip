@@ -20,6 +20,11 @@
 // four rounds over 256 CUs with the last 28% full; 54 tile-rows of 256 and 31
 // of 128 finish in about 3.6 rounds).
 //
+// Problems that these tiles would not spread over the CUs (chunks of a few
+// hundred to a few thousand tokens, narrow layers) take smaller or narrower
+// tiles with a deeper LDS ring instead (k_gemm_ring; pick_ring_tile has the
+// rule and the times on both sides).
+//
 // LDS layout: a stage holds BM rows of A and 256 rows of B, 64 elements (128
 // bytes = eight 16-byte slots) each; slot j of row r is stored at slot
 // j ^ ((r >> 1) & 7).  The LDS has 64 four-byte banks and serves a 16-byte
@@ -36,10 +41,11 @@
 // operand panels share an L2.
 //
 // Determinism: every output element is the sum over ascending 16-wide K
-// steps, one MFMA each, in the same sequence whatever M, BM, the row maps
-// or the tile position are; so chunked and unchunked calls, and either tile
-// height, agree bit for bit.
+// steps, one MFMA each, in the same sequence whatever M, the tile, the row
+// maps or the tile position are; so chunked and unchunked calls, and all
+// tiles, agree bit for bit.
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "device_common.h"
@@ -75,6 +81,7 @@ constexpr int NS = 2;                      // LDS pipeline stages
 constexpr int B_BYTES = BN * BK * 2;       // B bytes per stage
 constexpr int GROUP_M = 4;
 constexpr int NWAVES = 8;                  // 2 x 4 waves, two per SIMD
+constexpr int RING_GROUP_ROWS = 512;       // rows walked before the next columns (k_gemm_ring)
 constexpr int WN = BN * 2 / NWAVES;        // output columns per wave
 // slot swizzle of a 128-byte row (two rows share a 256-byte bank line)
 __host__ __device__ constexpr int row_swz(int r) { return (r >> 1) & 7; }
@@ -174,10 +181,10 @@ __device__ __forceinline__ float pair_sum(float v) {
 }
 
 // LDS bytes the QKV epilogue uses on a BM-row tile at head_dim HD: the
-// [BM] int4 token positions, at HD = 128 the [NWAVES][BM/2] partial sums of
-// squares, and the [BM][HD/2 + 2] float2 (cos, sin) rows.
-constexpr int qkv_epi_lds_bytes(int BM, int HD) {
-  return BM * 16 + (HD == 128 ? NWAVES * (BM / 2) * 4 : 0) + BM * (HD / 2 + 2) * 8;
+// [BM] int4 token positions, at HD = 128 the [NW][WR] partial sums of squares
+// (NW waves of WR rows each), and the [BM][HD/2 + 2] float2 (cos, sin) rows.
+constexpr int qkv_epi_lds_bytes(int BM, int HD, int NW = NWAVES, int WR = 0) {
+  return BM * 16 + (HD == 128 ? NW * (WR ? WR : BM / 2) * 4 : 0) + BM * (HD / 2 + 2) * 8;
 }
 
 // Epilogue of the QKV GEMM (EPI_QKV_HEADS at head_dim 64, EPI_QKV_HEADS_128
@@ -195,7 +202,7 @@ constexpr int qkv_epi_lds_bytes(int BM, int HD) {
 // transposed through LDS into [B, H, HD, Lp], 8 tokens per 16-byte store.
 // Rows are the tokens tok_begin + (m mod rows_per_batch) of batch row
 // m / rows_per_batch; nothing is written for m >= m_end.
-template <int MI, int NJ, int BM, int HD>
+template <int MI, int NJ, int BM, int HD, int NW, int WR>
 __device__ __forceinline__ void epilogue_qkv_heads(const GemmParams& p, const f32x16 (&acc)[MI][NJ],
                                                    int64_t m0, int64_t m_end, int n0, int wm, int wn,
                                                    int lane, int wave, uint8_t* smem,
@@ -236,15 +243,15 @@ __device__ __forceinline__ void epilogue_qkv_heads(const GemmParams& p, const f3
     // axis 0, 1 or 2 when it falls in that axis' range of the cumulative
     // dims/2 (table: axis-major, then position).
     constexpr int CS_STRIDE = NP + 2;  // float2 per padded row
-    constexpr int SS_BYTES = HALVES > 1 ? NWAVES * (BM / 2) * 4 : 0;
-    static_assert(qkv_epi_lds_bytes(BM, HD) == BM * 16 + SS_BYTES + BM * CS_STRIDE * 8, "LDS plan");
+    constexpr int SS_BYTES = HALVES > 1 ? NW * WR * 4 : 0;
+    static_assert(qkv_epi_lds_bytes(BM, HD, NW, WR) == BM * 16 + SS_BYTES + BM * CS_STRIDE * 8, "LDS plan");
     int4* pos_lds = reinterpret_cast<int4*>(smem);
     float* ss_lds = reinterpret_cast<float*>(smem + BM * 16);
     float2* cs_lds = reinterpret_cast<float2*>(smem + BM * 16 + SS_BYTES);
     __syncthreads();  // every wave is done reading the operand stages
     {
       const int gw = max(a.geom.grid[2], 1), hw = max(a.geom.grid[1] * a.geom.grid[2], 1);
-      for (int t = (int)threadIdx.x; t < BM; t += NWAVES * 64) {
+      for (int t = (int)threadIdx.x; t < BM; t += NW * 64) {
         const int64_t m = m0 + t;
         const bool valid = m < m_end;
         const int64_t bb = valid ? m / rpb : 0;
@@ -258,7 +265,7 @@ __device__ __forceinline__ void epilogue_qkv_heads(const GemmParams& p, const f3
     {
       const int np0 = a.geom.dims[0] / 2, np1 = a.geom.dims[1] / 2, np2 = a.geom.dims[2] / 2;
       const int tb1 = a.geom.grid[0] * np0, tb2 = tb1 + a.geom.grid[1] * np1;
-      for (int e = (int)threadIdx.x; e < BM * NP; e += NWAVES * 64) {
+      for (int e = (int)threadIdx.x; e < BM * NP; e += NW * 64) {
         const int t = e / NP, pr = e % NP;
         const int4 ps = pos_lds[t];
         int idx = -1;
@@ -283,13 +290,13 @@ __device__ __forceinline__ void epilogue_qkv_heads(const GemmParams& p, const f3
               ss = fmaf(v, v, ss);
             }
         ss = pair_sum(ss);
-        if (hi == 0) ss_lds[wave * (BM / 2) + i * 32 + r32] = ss;
+        if (hi == 0) ss_lds[wave * WR + i * 32 + r32] = ss;
       }
     }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-      const int64_t m = m0 + wm * (BM / 2) + i * 32 + r32;
+      const int64_t m = m0 + wm * WR + i * 32 + r32;
       const bool valid = m < m_end;
       const int64_t bb = valid ? m / rpb : 0;
       const int tok = a.tok_begin + (int)(valid ? m - bb * rpb : 0);
@@ -306,14 +313,14 @@ __device__ __forceinline__ void epilogue_qkv_heads(const GemmParams& p, const f3
           }
       if constexpr (HALVES > 1) {
         // dims 0..63 (wave wave - half) plus dims 64..127, in that order
-        const float* sp = ss_lds + (wave - half) * (BM / 2) + i * 32 + r32;
-        ss = sp[0] + sp[BM / 2];
+        const float* sp = ss_lds + (wave - half) * WR + i * 32 + r32;
+        ss = sp[0] + sp[WR];
       } else {
         ss = pair_sum(ss);
       }
       // 1/sqrt(mean + eps) with the hardware reciprocal square root (1 ulp)
       const float r = __builtin_amdgcn_rsqf(ss * (1.0f / (float)HD) + a.qk_eps);
-      const float2* csr = cs_lds + (wm * (BM / 2) + i * 32 + r32) * CS_STRIDE + half * 32 + 2 * hi;
+      const float2* csr = cs_lds + (wm * WR + i * 32 + r32) * CS_STRIDE + half * 32 + 2 * hi;
       f16* row = dst + (((int64_t)bb * a.heads + h) * Lp + tok) * HD + half * 64;
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
@@ -344,12 +351,12 @@ __device__ __forceinline__ void epilogue_qkv_heads(const GemmParams& p, const f3
 
   // V: every wave has finished reading the operand stages before they hold
   // the transposed blocks (16 KiB per wave at BM = 256)
-  constexpr int TPW = BM / 2;  // tokens of this wave's block
+  constexpr int TPW = WR;     // tokens of this wave's block
   __syncthreads();
   f16* lds = reinterpret_cast<f16*>(smem) + wave * 64 * TPW;   // [64 dims][TPW tokens]
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
-    const bool valid = m0 + wm * (BM / 2) + i * 32 + r32 < m_end;
+    const bool valid = m0 + wm * WR + i * 32 + r32 < m_end;
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -388,6 +395,106 @@ __device__ __forceinline__ void epilogue_qkv_heads(const GemmParams& p, const f3
 }
 
 }  // namespace
+
+// Epilogue of a BM-row tile of NW waves, each holding WR = 32 MI rows and 64
+// columns: the QKV heads, or bias (+ GELU | gated residual) and the stores.
+template <int EPI, typename CT, typename RT, int MI, int NJ, int BM, int NW, int WR>
+__device__ __forceinline__ void store_tile(const GemmParams& p, const f32x16 (&acc)[MI][NJ], int64_t m0,
+                                           int64_t m_end, int n0, int wm, int wn, int lane, int wave,
+                                           uint8_t* smem_raw, const uint16_t* __restrict__ bias,
+                                           CT* __restrict__ cout, const RT* __restrict__ resid,
+                                           const float* __restrict__ gate) {
+  constexpr int WN = 32 * NJ;
+  const int r32 = lane & 31, hi = lane >> 5;
+  if constexpr (EPI == EPI_QKV_HEADS || EPI == EPI_QKV_HEADS_128) {
+    epilogue_qkv_heads<MI, NJ, BM, EPI == EPI_QKV_HEADS ? 64 : 128, NW, WR>(p, acc, m0, m_end, n0, wm, wn, lane, wave,
+                                                                            smem_raw, bias);
+    return;
+  }
+
+  // Epilogue.  acc[i][j][r] = C[m][n] with m = m0 + wm*WR + i*32 + r32 and
+  // n = n0 + wn*64 + j*32 + 8*(r/4) + 4*hi + r%4.  Every input of a row group
+  // is loaded before any of its stores (the pointers are restrict), so the
+  // loads overlap instead of each paying a full memory latency.
+  float bv[NJ][4][4];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      load4f<uint16_t>(bias + n0 + wn * WN + j * 32 + 8 * q + 4 * hi, bv[j][q]);
+  const int64_t rpb = p.c_map.rows_per_batch;
+  bool bad = false;  // an fp16 result at or beyond the fp16 range
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    const int64_t m = m0 + wm * WR + i * 32 + r32;
+    if (m >= m_end) continue;
+    const int64_t b = m / rpb;
+    const int64_t within = m - b * rpb;
+    const int64_t crow = b * p.c_map.batch_stride + p.c_map.row_offset + within;
+    CT* crow_ptr = cout + crow * p.ldc;
+    float v[NJ][4][4];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[j][q][e] = acc[i][j][4 * q + e] + bv[j][q][e];
+    if (EPI == XEMA_EPI_GATED_RESIDUAL) {
+      const int64_t rrow = b * p.resid_map.batch_stride + p.resid_map.row_offset + within;
+      const RT* rrow_ptr = resid + rrow * p.ld_resid;
+      const float* grow = gate + b * p.gate_stride +
+                          (p.gate_sel.pos_offset + within < p.gate_sel.text_len ? p.gate_sel.text_delta : 0);
+      float res[NJ][4][4];
+      f32x4 g[NJ][4];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int n = n0 + wn * WN + j * 32 + 8 * q + 4 * hi;
+          load4f<RT>(rrow_ptr + n, res[j][q]);
+          g[j][q] = *reinterpret_cast<const f32x4*>(grow + n);
+        }
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[j][q][e] = fmaf(g[j][q][e], v[j][q][e], res[j][q][e]);
+    }
+    if (EPI == XEMA_EPI_BIAS_GELU) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[j][q][e] = gelu_tanh(v[j][q][e]);
+    }
+    if constexpr (sizeof(CT) == 2) {
+      typedef CT c4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; q += 2) {
+          c4 a, b;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float y0 = as_rounded_f32(v[j][q][e]), y1 = as_rounded_f32(v[j][q + 1][e]);
+            if constexpr (__is_same(CT, f16)) bad |= !fits_f16(y0) || !fits_f16(y1);
+            a[e] = from_f32<CT>(y0);
+            b[e] = from_f32<CT>(y1);
+          }
+          store_group_pair<CT>(crow_ptr + n0 + wn * WN + j * 32 + 8 * q, a, b, hi, true);
+        }
+    } else {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          store4<CT>(crow_ptr + n0 + wn * WN + j * 32 + 8 * q + 4 * hi, v[j][q]);
+    }
+  }
+  raise_flag(p.status, bad);
+}
 
 // One BM x 256 output tile.  EPI: XEMA_EPI_BIAS / XEMA_EPI_BIAS_GELU (CT =
 // bf16 or f16) or XEMA_EPI_GATED_RESIDUAL (CT = float, RT = residual element
@@ -561,103 +668,201 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int64_t m_begin, 
   // before the workgroup can end
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
 
-  if constexpr (EPI == EPI_QKV_HEADS || EPI == EPI_QKV_HEADS_128) {
-    epilogue_qkv_heads<MI, NJ, BM, EPI == EPI_QKV_HEADS ? 64 : 128>(p, acc, m0, m_end, n0, wm, wn, lane,
-                                                                   wave, smem_raw, bias);
-    return;
-  }
-
-  // Epilogue.  acc[i][j][r] = C[m][n] with m = m0 + wm*(BM/2) + i*32 + r32 and
-  // n = n0 + wn*64 + j*32 + 8*(r/4) + 4*hi + r%4.  Every input of a row group
-  // is loaded before any of its stores (the pointers are restrict), so the
-  // loads overlap instead of each paying a full memory latency.
-  float bv[NJ][4][4];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j)
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      load4f<uint16_t>(bias + n0 + wn * WN + j * 32 + 8 * q + 4 * hi, bv[j][q]);
-  const int64_t rpb = p.c_map.rows_per_batch;
-  bool bad = false;  // an fp16 result at or beyond the fp16 range
-#pragma unroll
-  for (int i = 0; i < MI; ++i) {
-    const int64_t m = m0 + wm * (BM / 2) + i * 32 + r32;
-    if (m >= m_end) continue;
-    const int64_t b = m / rpb;
-    const int64_t within = m - b * rpb;
-    const int64_t crow = b * p.c_map.batch_stride + p.c_map.row_offset + within;
-    CT* crow_ptr = cout + crow * p.ldc;
-    float v[NJ][4][4];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[j][q][e] = acc[i][j][4 * q + e] + bv[j][q][e];
-    if (EPI == XEMA_EPI_GATED_RESIDUAL) {
-      const int64_t rrow = b * p.resid_map.batch_stride + p.resid_map.row_offset + within;
-      const RT* rrow_ptr = resid + rrow * p.ld_resid;
-      const float* grow = gate + b * p.gate_stride +
-                          (p.gate_sel.pos_offset + within < p.gate_sel.text_len ? p.gate_sel.text_delta : 0);
-      float res[NJ][4][4];
-      f32x4 g[NJ][4];
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int n = n0 + wn * WN + j * 32 + 8 * q + 4 * hi;
-          load4f<RT>(rrow_ptr + n, res[j][q]);
-          g[j][q] = *reinterpret_cast<const f32x4*>(grow + n);
-        }
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[j][q][e] = fmaf(g[j][q][e], v[j][q][e], res[j][q][e]);
-    }
-    if (EPI == XEMA_EPI_BIAS_GELU) {
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[j][q][e] = gelu_tanh(v[j][q][e]);
-    }
-    if constexpr (sizeof(CT) == 2) {
-      typedef CT c4 __attribute__((ext_vector_type(4)));
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; q += 2) {
-          c4 a, b;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float y0 = as_rounded_f32(v[j][q][e]), y1 = as_rounded_f32(v[j][q + 1][e]);
-            if constexpr (__is_same(CT, f16)) bad |= !fits_f16(y0) || !fits_f16(y1);
-            a[e] = from_f32<CT>(y0);
-            b[e] = from_f32<CT>(y1);
-          }
-          store_group_pair<CT>(crow_ptr + n0 + wn * WN + j * 32 + 8 * q, a, b, hi, true);
-        }
-    } else {
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          store4<CT>(crow_ptr + n0 + wn * WN + j * 32 + 8 * q + 4 * hi, v[j][q]);
-    }
-  }
-  raise_flag(p.status, bad);
+  store_tile<EPI, CT, RT, MI, NJ, BM, NWAVES, BM / 2>(p, acc, m0, m_end, n0, wm, wn, lane, wave, smem_raw, bias, cout,
+                                                  resid, gate);
 }
 
-// Rows [0, split) go in 256-row tiles, rows [split, M) in 128-row tiles.  The
-// split minimises an estimate of the time in units of one wave of 256-row
-// tiles over the 256 CUs: a wave of 128-row tiles costs 0.62 (measured: the
-// half-height tile does half the MFMA work at lower efficiency), and a
-// second launch behind the first costs about 3072/K waves (its start-up and
-// the first launch's drain, measured at roughly 50 us).  E.g. 17776 x 3072 x
-// 12288: 840 tiles = 4 waves, or 768 + 132 half tiles = 3 + 0.62 + 0.25.
+// A BM x BN output tile, BN = 32 NJ WNW, for problems whose 256-column tiles
+// would leave CUs idle: WMW x WNW waves of (BM/WMW) x 32 NJ, an NS-stage ring
+// of 64-wide K steps, the same swizzled LDS rows, and the same MFMA sequence
+// per output element as gemm_tile, so the results are its bits.
+//
+// What bounds the small tiles is the fetch: a CU gets about 55 GB/s of operand
+// rows from beyond its L2 (93-128 GB/s from L2), whatever the number of loads
+// in flight past about 48 KB, the access order within a row, or the number of
+// waves; with the loads alone a 128 x 128 tile takes the same 0.54 us a step
+// as the whole loop.  Hence tiles as large as still give each CU one, and a
+// ring deep enough for that much in flight.
+//
+// Where the registers allow it, a wave reads all fragments of step kt+1 from
+// LDS while the MFMAs of step kt run (64 x 64 tiles at K = 3072: 17 -> 13 us
+// against one k-step ahead).  The barrier before them means that every wave
+// holds step kt in registers, so its stage is free for step kt + NS, and that
+// step kt+1 has landed, while the NS - 2 steps after it may be in flight.
+template <typename T, int EPI, typename CT, typename RT, int BM, int WMW, int WNW, int NJ_, int NS_>
+__device__ __forceinline__ void gemm_ring_tile(const GemmParams& p, int wg, uint8_t* smem_raw,
+                                               const uint16_t* __restrict__ bias, CT* __restrict__ cout,
+                                               const RT* __restrict__ resid, const float* __restrict__ gate) {
+  constexpr int NW = WMW * WNW, WCOLS = 32 * NJ_, BN_ = WNW * WCOLS;
+  constexpr int WR = BM / WMW;
+  constexpr int MI = WR / 32;
+  constexpr int A_BYTES = BM * ROWB, STAGE_BYTES = A_BYTES + BN_ * ROWB;
+  constexpr int A_LOADS = BM / NW / RPL, B_LOADS = BN_ / NW / RPL;
+  static_assert(MI * 32 * WMW == BM && A_LOADS * NW * RPL == BM && B_LOADS * NW * RPL == BN_, "tile split");
+  static_assert(NS_ >= 2, "ring");
+  constexpr int LPS = A_LOADS + B_LOADS;
+  typedef typename Mfma<T>::frag frag;
+
+  const int K = p.K;
+  const int KT = K / BK;
+  const int tiles_m = (int)((p.M + BM - 1) / BM);
+  const int tiles_n = p.N / BN_;
+  const int total = tiles_m * tiles_n;
+  // each XCD walks a contiguous range of tiles, rows fastest in groups of
+  // RING_GROUP_ROWS rows, so that a weight panel is read by few XCDs
+  constexpr int GM = RING_GROUP_ROWS / BM;
+  const int xcd = wg & 7, slot = wg >> 3;
+  const int per = total >> 3, rem = total & 7;
+  const int t = xcd * per + min(xcd, rem) + slot;
+  const int group = t / (GM * tiles_n);
+  const int first_m = group * GM;
+  const int gsize = min(tiles_m - first_m, GM);
+  const int in_group = t - group * GM * tiles_n;
+  const int64_t m0 = (int64_t)(first_m + in_group % gsize) * BM;
+  const int n0 = (in_group / gsize) * BN_;
+
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WNW, wn = wave % WNW;
+
+  const T* A = reinterpret_cast<const T*>(p.a);
+  const T* Bw = reinterpret_cast<const T*>(p.b);
+  const __amdgpu_buffer_rsrc_t ra = make_rsrc(A + m0 * K, min<int64_t>(BM, p.M - m0) * K * 2);
+  const __amdgpu_buffer_rsrc_t rb = make_rsrc(Bw + (int64_t)n0 * K, (int64_t)BN_ * K * 2);
+
+  uint32_t a_off[A_LOADS], b_off[B_LOADS];
+#pragma unroll
+  for (int c = 0; c < A_LOADS; ++c) {
+    const int row = (wave * A_LOADS + c) * RPL + lane / SLOTS;
+    a_off[c] = (uint32_t)((row * K + (((lane % SLOTS) ^ row_swz(row)) * 8)) * 2);
+  }
+#pragma unroll
+  for (int c = 0; c < B_LOADS; ++c) {
+    const int row = (wave * B_LOADS + c) * RPL + lane / SLOTS;
+    b_off[c] = (uint32_t)((row * K + (((lane % SLOTS) ^ row_swz(row)) * 8)) * 2);
+  }
+  // the loads of step kt into the stage at st (a step past the last one
+  // reloads the last, so that the count of loads in flight stays fixed)
+  auto issue = [&](int kt, uint8_t* st) {
+    const uint32_t kbyte = (uint32_t)((kt < KT ? kt : KT - 1) * BK * 2);
+#pragma unroll
+    for (int c = 0; c < A_LOADS; ++c) load_lds16(ra, st + (wave * A_LOADS + c) * 1024, a_off[c], kbyte);
+#pragma unroll
+    for (int c = 0; c < B_LOADS; ++c)
+      load_lds16(rb, st + A_BYTES + (wave * B_LOADS + c) * 1024, b_off[c], kbyte);
+  };
+
+  f32x16 acc[MI][NJ_];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ_; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  const int r32 = lane & 31, hi = lane >> 5, sw = row_swz(r32);
+  const int a_row0 = (wm * WR + r32) * ROWB;
+  const int b_row0 = A_BYTES + (wn * WCOLS + r32) * ROWB;
+  // fragments of NB k-steps: two whole steps where the registers allow it, so
+  // that a step's LDS reads run a step ahead of its MFMAs, else two k-steps
+  constexpr bool WHOLE = KS * (MI + NJ_) * 8 + MI * NJ_ * 16 + 48 <= (NW <= 4 ? 512 : 256);
+  constexpr int NB = WHOLE ? 2 * KS : 2;
+  frag fx[NB][MI], fw[NB][NJ_];
+  auto read = [&](const uint8_t* st, int kk, int to) {
+    const int so = (((kk * 2 + hi) ^ sw) * 16);
+#pragma unroll
+    for (int j = 0; j < NJ_; ++j) fw[to][j] = *reinterpret_cast<const frag*>(st + b_row0 + j * 32 * ROWB + so);
+#pragma unroll
+    for (int i = 0; i < MI; ++i) fx[to][i] = *reinterpret_cast<const frag*>(st + a_row0 + i * 32 * ROWB + so);
+  };
+  auto mfmas = [&](int from) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ_; ++j) acc[i][j] = Mfma<T>::run(fw[from][j], fx[from][i], acc[i][j]);
+  };
+  // nr LDS reads and nl loads spread over nm MFMAs: issued together, the loads
+  // of all waves fill the address queue and hold the MFMAs back
+  auto interleave = [](auto nm, auto nr, auto nl) {
+#pragma unroll
+    for (int g = 0; g < nm(); ++g) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+#pragma unroll
+      for (int n = g * nr() / nm(); n < (g + 1) * nr() / nm(); ++n) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+#pragma unroll
+      for (int n = g * nl() / nm(); n < (g + 1) * nl() / nm(); ++n) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    }
+  };
+  auto barrier_landed = [&]() {  // all but the newest NS - 2 steps' loads have landed
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS_ - 2) * LPS));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  int cur = 0;  // the stage of step kt
+  // step kt, h = kt & 1: the barrier means that every wave has read all of its
+  // stage, and that step kt+1 has landed
+  auto step = [&](int kt, int h) {
+    uint8_t* st = smem_raw + cur * STAGE_BYTES;
+    cur = cur + 1 == NS_ ? 0 : cur + 1;
+    if constexpr (!WHOLE) {
+#pragma unroll
+      for (int kk = 0; kk < KS - 1; ++kk) {
+        read(st, kk + 1, (kk + 1) & 1);
+        mfmas(kk & 1);
+        interleave(std::integral_constant<int, MI * NJ_>(), std::integral_constant<int, MI + NJ_>(),
+                   std::integral_constant<int, 0>());
+      }
+    }
+    barrier_landed();
+    issue(kt + NS_, st);
+    const uint8_t* next = smem_raw + cur * STAGE_BYTES;
+    if constexpr (WHOLE) {
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk) read(next, kk, (h ^ 1) * KS + kk);
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk) mfmas(h * KS + kk);
+      interleave(std::integral_constant<int, KS * MI * NJ_>(), std::integral_constant<int, KS * (MI + NJ_)>(),
+                 std::integral_constant<int, LPS>());
+    } else {
+      read(next, 0, 0);
+      mfmas((KS - 1) & 1);
+      interleave(std::integral_constant<int, MI * NJ_>(), std::integral_constant<int, MI + NJ_>(),
+                 std::integral_constant<int, LPS>());
+    }
+  };
+
+#pragma unroll
+  for (int s = 0; s < NS_ - 1; ++s) issue(s, smem_raw + s * STAGE_BYTES);
+  barrier_landed();  // step 0 has landed
+  issue(NS_ - 1, smem_raw + (NS_ - 1) * STAGE_BYTES);
+#pragma unroll
+  for (int kk = 0; kk < (WHOLE ? KS : 1); ++kk) read(smem_raw, kk, kk);
+  int kt = 0;
+  for (; kt + 1 < KT; kt += 2) {
+    step(kt, 0);
+    step(kt + 1, 1);
+  }
+  if (kt < KT) step(kt, 0);
+  // the last iterations' loads still write to LDS, which the epilogue reuses
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+
+  store_tile<EPI, CT, RT, MI, NJ_, BM, NW, WR>(p, acc, m0, p.M, n0, wm, wn, lane, wave, smem_raw, bias, cout, resid, gate);
+}
+
+template <typename T, int EPI, typename CT, typename RT, int BM, int WMW, int WNW, int NJ_, int NS_>
+__global__ __launch_bounds__(WMW * WNW * 64, 1) void k_gemm_ring(GemmParams p, const uint16_t* __restrict__ bias,
+                                                            CT* __restrict__ cout, const RT* __restrict__ resid,
+                                                            const float* __restrict__ gate) {
+  constexpr int STAGES = NS_ * (BM + WNW * 32 * NJ_) * ROWB;
+  constexpr int HD = EPI == EPI_QKV_HEADS_128 ? 128 : 64;
+  constexpr int EPI_LDS = EPI == EPI_QKV_HEADS || EPI == EPI_QKV_HEADS_128
+                              ? qkv_epi_lds_bytes(BM, HD, WMW * WNW, BM / WMW) : 0;
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[STAGES > EPI_LDS ? STAGES : EPI_LDS];
+  gemm_ring_tile<T, EPI, CT, RT, BM, WMW, WNW, NJ_, NS_>(p, (int)blockIdx.x, smem, bias, cout, resid, gate);
+}
+
 // One launch, two tile heights: 256-row tiles of rows [0, split) and
 // 128-row tiles of rows [split, M).  The first `first_small` workgroups take
 // half-height tiles, the next tiles_big the full tiles, the rest the other
@@ -716,8 +921,8 @@ static double tile_makespan(int64_t n_big, int64_t n_small, double half) {
 
 // Rows [0, split) go to 256-row tiles, the rest to 128-row tiles: the split
 // with the least modelled completion time, a half-height tile costing 0.62 of
-// a full one (measured).  Small M runs 128-row tiles only.
-static int64_t gemm_row_split(int64_t M, int tiles_n) {
+// a full one (measured).  *rounds receives that time in full tiles.
+static int64_t gemm_row_split(int64_t M, int tiles_n, double* rounds) {
   const int64_t tm = (M + 255) / 256;
   int64_t best_split = M;
   double best = tile_makespan(tm * tiles_n, 0, 0.62);
@@ -726,13 +931,77 @@ static int64_t gemm_row_split(int64_t M, int tiles_n) {
     const double cost = tile_makespan(t1 * tiles_n, rest * tiles_n, 0.62);
     if (cost < best - 1e-9) { best = cost; best_split = t1 * 256; }
   }
+  *rounds = best;
   return best_split;
+}
+
+// The tiles of k_gemm_ring, with the microseconds one 64-wide K step of a tile
+// takes when the 256 CUs hold about one each (measured at K = 3072 and 12288;
+// a CU fetches about 55 GB/s from beyond its L2, so the small tiles cost their
+// operand bytes and only the 256-row ones their MFMAs).  A problem whose
+// 256 x 256 tiles do not fill a few rounds of the CUs takes the tile with the
+// fewest rounds x step cost; measured against the 256-column tiles alone:
+//   512 x 3072 x 3072     64 x 128    50 -> 20 us
+//   1000 x 3072 x 12288   128 x 96   232 -> 106 us
+//   2048 x 3072 x 12288   128 x 192  241 -> 158 us
+//   2048 x 12288 x 3072   256 x 192  187 -> 154 us
+//   256 x 3072 x 12288    64 x 64    159 -> 46 us
+//   4608 x 3072 x 3072    256 x 256  105 us (128 x 192: 128, 256 x 128: 113)
+enum RingTile { R256x192, R256x128, R128x192, R128x128, R128x96, R64x128, R64x64, N_RING_TILES };
+struct RingCost { int rows, cols; double step_us; };
+static const RingCost kRingCost[N_RING_TILES] = {
+    {256, 192, 1.45}, {256, 128, 1.0}, {128, 192, 0.8}, {128, 128, 0.6}, {128, 96, 0.52}, {64, 128, 0.38}, {64, 64, 0.25}};
+constexpr double FULL_STEP_US = 1.7;  // of the 256 x 256 tile
+
+// The ring tile for an M x N problem, or -1 for the 256-column tiles (whose
+// modelled time is `rounds` full tiles).  heads_dim: 64 or 128 for the QKV
+// epilogue, which needs 64 columns a wave and, at 128, two waves a row.
+static int pick_ring_tile(int64_t M, int N, double rounds, int heads_dim) {
+  int best = -1;
+  double cost = 0.95 * rounds * FULL_STEP_US;  // a modelled gain below 5% is none
+  for (int t = 0; t < N_RING_TILES; ++t) {
+    const RingCost& c = kRingCost[t];
+    if (N % c.cols) continue;
+    if (heads_dim && c.cols != 128 && !(heads_dim == 64 && t == R64x64)) continue;
+    const int64_t tiles = ((M + c.rows - 1) / c.rows) * (N / c.cols);
+    const double us = (double)((tiles + 255) / 256) * c.step_us;
+    if (us < cost - 1e-9) { cost = us; best = t; }
+  }
+  return best;
+}
+
+template <typename T, int EPI, typename CT, typename RT, int BM, int WMW, int WNW, int NJ_, int NS_>
+static hipError_t launch_ring(const GemmParams& p, hipStream_t s) {
+  const int64_t tiles = ((p.M + BM - 1) / BM) * (p.N / (WNW * 32 * NJ_));
+  hipLaunchKernelGGL((k_gemm_ring<T, EPI, CT, RT, BM, WMW, WNW, NJ_, NS_>), dim3((unsigned)tiles),
+                     dim3(WMW * WNW * 64), 0, s, p, p.bias, (CT*)p.c, (const RT*)p.resid, p.gate);
+  return hipGetLastError();
 }
 
 template <typename T, int EPI, typename CT, typename RT>
 static hipError_t launch_t(const GemmParams& p, hipStream_t s) {
   const int tiles_n = p.N / BN;
-  const int64_t split = gemm_row_split(p.M, tiles_n);
+  double rounds;
+  const int64_t split = gemm_row_split(p.M, tiles_n, &rounds);
+  constexpr int HD = EPI == EPI_QKV_HEADS ? 64 : EPI == EPI_QKV_HEADS_128 ? 128 : 0;
+  switch (pick_ring_tile(p.M, p.N, rounds, HD)) {
+    case R256x128: return launch_ring<T, EPI, CT, RT, 256, 4, 2, 2, 3>(p, s);
+    case R128x128: return launch_ring<T, EPI, CT, RT, 128, 2, 2, 2, 4>(p, s);
+    case R64x128: return launch_ring<T, EPI, CT, RT, 64, 2, 2, 2, 3>(p, s);
+    case R64x64:
+      if constexpr (HD != 128) return launch_ring<T, EPI, CT, RT, 64, 2, 1, 2, 4>(p, s);
+      break;
+    case R256x192:
+      if constexpr (HD == 0) return launch_ring<T, EPI, CT, RT, 256, 4, 2, 3, 2>(p, s);
+      break;
+    case R128x192:
+      if constexpr (HD == 0) return launch_ring<T, EPI, CT, RT, 128, 2, 2, 3, 3>(p, s);
+      break;
+    case R128x96:
+      if constexpr (HD == 0) return launch_ring<T, EPI, CT, RT, 128, 4, 1, 3, 4>(p, s);
+      break;
+    default: break;
+  }
   const int64_t big = ((split + 255) / 256) * tiles_n;
   const int64_t small = ((p.M - split + 127) / 128) * tiles_n;
   // Up to 192 half-height tiles first (a multiple of 8, so that each set of
