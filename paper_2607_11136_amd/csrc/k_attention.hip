@@ -47,6 +47,8 @@
 // Workgroups: NW = 8 waves = 8 * QB * 32 queries of one (batch, head).  The
 // grid is 1-D and remapped so that all query blocks of a head run on one XCD
 // and share its L2 copy of K and V.
+#include <type_traits>
+
 #include "attention.h"
 #include "device_common.h"
 
@@ -61,6 +63,9 @@ constexpr float PMAX = 4096.0f; // bound on a lane's P sum over a tile before th
 // (16 more VGPRs per query column) or is subtracted before the exponential.
 constexpr bool minit_in_mfma(int qb) { return qb <= 1; }
 constexpr int BUF_FLAGS = 0x00020000;
+
+// s_waitcnt immediate that waits until at most n vector memory operations are in flight, and for all LDS accesses
+constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, int64_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes,
@@ -668,6 +673,136 @@ __global__ __launch_bounds__(NW * 64) void k_attention_lazy(AttnParams p) {
   }
 }
 
+// The kernels above for launches that do not fill the CUs: NW waves of one
+// query column block each and a ring of NST stages, loads NST - 1 tiles ahead.
+// With one or two waves on a SIMD a tile is bound by its own chain (scores,
+// exponentials, P V^T: about 0.6 us at d = 64 and 1 us at d = 128 for a wave
+// alone, 0.85 us for two, against 1.4 us for the two of two columns each), so
+// spreading the waves over more SIMDs is what shortens the launch.  Each
+// column's arithmetic is that of the kernel for its width, so the output is
+// the same bit for bit.
+template <int HD, int NW, int NST>
+__global__ __launch_bounds__(NW * 64, HD == 64 ? 3 : 2) void k_attention_ring(AttnParams p) {
+  constexpr int K_BYTES = KV * HD * 2;
+  constexpr int STAGE = 2 * K_BYTES;
+  constexpr int NKK = HD / 16;
+  constexpr int QWG = 32 * NW;
+  constexpr int LPT = K_BYTES / 1024 / NW;    // loads per wave of a K or a V^T tile
+  static_assert(LPT * NW * 1024 == K_BYTES && NST >= 2, "load split");
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[NST * STAGE];
+
+  const int nqb = (p.q_count + QWG - 1) / QWG;
+  const int total = nqb * p.heads * p.batch;
+  const int wg = blockIdx.x;
+  const int xcd = wg & 7, slot = wg >> 3;
+  const int per = total >> 3, rem = total & 7;
+  const int t = xcd * per + min(xcd, rem) + slot;
+  const int qb = t % nqb;
+  const int bh = t / nqb;                     // b * heads + h
+  const int b = bh / p.heads, h = bh - b * p.heads;
+
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r32 = lane & 31, hi = lane >> 5;
+  const int64_t Lp = p.padded_len;
+
+  const f16* Qh = p.q + (int64_t)bh * Lp * HD;
+  const __amdgpu_buffer_rsrc_t rk = make_rsrc(p.k + (int64_t)bh * Lp * HD, Lp * HD * 2);
+  const __amdgpu_buffer_rsrc_t rv = make_rsrc(p.vt + (int64_t)bh * HD * Lp, (int64_t)HD * Lp * 2);
+
+  uint32_t k_off[LPT], v_off[LPT];
+#pragma unroll
+  for (int j = 0; j < LPT; ++j) {
+    const int byte = (wave + NW * j) * 1024 + lane * 16;
+    const int row = byte / (2 * HD), ps = (byte % (2 * HD)) / 16;
+    k_off[j] = (uint32_t)((row * HD + ((ps ^ swz_k<HD>(row)) * 8)) * 2);
+    const int vrow = (wave + NW * j) * 8 + (lane >> 3);
+    v_off[j] = (uint32_t)((vrow * Lp + ((lane & 7) ^ swz_v(vrow)) * 8) * 2);
+  }
+
+  const int q_first = p.q_begin + qb * QWG + wave * 32;
+  f16x8 qf[1][NKK];
+  {
+    const int q = min(q_first + r32, (int)Lp - 1);
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk)
+      qf[0][kk] = *reinterpret_cast<const f16x8*>(Qh + (int64_t)q * HD + kk * 16 + hi * 8);
+  }
+
+  WaveState<HD, 1> st;
+  st.mrow[0] = 0.f;
+  st.lrow[0] = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) st.minit[0][r] = 0.f;
+#pragma unroll
+  for (int d = 0; d < HD / 32; ++d)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) st.oacc[0][d][r] = 0.f;
+
+  const int krow = kappa(r32);
+  const int kswz = swz_k<HD>(krow);
+  const int nkv = (p.seq_len + KV - 1) / KV;
+  const int tail = p.seq_len - (nkv - 1) * KV;
+
+  // (a tile past the last one reloads the last, so that the count of loads in
+  // flight stays fixed)
+  auto issue = [&](int kv, int stage) {
+    const int kc = min(kv, nkv - 1);
+    issue_kv<LPT, LPT, K_BYTES, NW>(rk, rv, k_off, v_off, smem + stage * STAGE, wave, (uint32_t)(kc * KV * HD * 2),
+                                    (uint32_t)(kc * KV * 2));
+  };
+  int cur = 0;   // the stage of tile kv
+  // the barrier: tile kv has landed, and every wave is done with tile kv-1,
+  // whose stage tile kv+NST-1 goes to
+  auto tile = [&](int kv, auto last) {
+    constexpr bool LAST = decltype(last)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 2) * 2 * LPT));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (!LAST) issue(kv + NST - 1, cur == 0 ? NST - 1 : cur - 1);
+    const uint8_t* Ks = smem + cur * STAGE;
+    cur = cur + 1 == NST ? 0 : cur + 1;
+    f16x8 pf[1][2][2];
+    if constexpr (HD == 64) {
+      f32x16 sc[2][1];
+      tile_scores<HD, 1, true>(Ks, qf, st.minit, krow, kswz, hi, sc);
+      f32x16 s[2] = {sc[0][0], sc[1][0]};
+      if (LAST && tail < KV) mask_tail_col(s, tail, hi);
+      float lsp = exp_pack<false>(s[0], s[1], 0.f, pf[0]);
+      if (__builtin_amdgcn_ballot_w64(kv == 0 || lsp > PMAX)) rescale_col<HD, 1>(s, kv == 0, 0, lsp, st, pf[0], hi);
+      st.lrow[0] += lsp;
+    } else {
+      f32x16 s[2][1];
+      tile_scores<HD, 1, true>(Ks, qf, st.minit, krow, kswz, hi, s);
+      if (LAST && tail < KV) mask_tail<1>(s, tail, hi);
+      tile_softmax<HD, 1>(s, kv == 0, st, pf);
+    }
+    tile_pv<HD, 1>(Ks + K_BYTES, pf, r32, hi, st.oacc);
+  };
+#pragma unroll
+  for (int k = 0; k < NST - 1; ++k) issue(k, k);
+  for (int kv = 0; kv < nkv - 1; ++kv) tile(kv, std::false_type());
+  tile(nkv - 1, std::true_type());
+  // reloads may still be writing to LDS: let them finish before the workgroup ends
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+
+  const int q = q_first + r32;
+  const float inv = 1.0f / pair_sum(st.lrow[0]);
+  if (q >= p.q_begin + p.q_count) return;
+  f16* orow = p.o + ((int64_t)b * p.q_count + (q - p.q_begin)) * ((int64_t)p.heads * HD) + (int64_t)h * HD;
+#pragma unroll
+  for (int d = 0; d < HD / 32; ++d)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      f16x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = (f16)(st.oacc[0][d][4 * g + e] * inv);
+      *reinterpret_cast<f16x4*>(orow + d * 32 + 8 * g + 4 * hi) = o;
+    }
+}
+
 template <int HD, int QB, int NW, bool LAZY>
 static hipError_t launch_t(const AttnParams& p, hipStream_t s) {
   constexpr int QWG = QB * 32 * NW;
@@ -681,9 +816,40 @@ static hipError_t launch_t(const AttnParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int HD, int NW, int NST>
+static hipError_t launch_ring(const AttnParams& p, hipStream_t s) {
+  const int64_t total = (int64_t)((p.q_count + 32 * NW - 1) / (32 * NW)) * p.heads * p.batch;
+  hipLaunchKernelGGL((k_attention_ring<HD, NW, NST>), dim3((unsigned)total), dim3(NW * 64), 0, s, p);
+  return hipGetLastError();
+}
+
+// The kernel and its queries per workgroup by the rounds a launch takes over
+// the 256 CUs.  Times are relative to a round of the kernel with the largest
+// workgroups (48 heads of 8192 keys, 0.18 ms; 24 of 4608 at d = 128, 0.10 ms):
+//   d = 64:   512 queries 1; 256 queries 0.62; 128 queries 0.44, 0.74 or 1.09
+//             with one, two or three workgroups on a CU
+//   d = 128:  256 queries 1; 128 queries 0.75, worth it only while each CU
+//             has one (two on a CU take 1.15) or when the larger ones would
+//             start a second round that is nearly empty
+// Measured, larger and chosen: d = 64, 48 heads, 1000 queries of 17776 keys
+// 379 -> 256 us, 128 of 8192 178 -> 79 us, 3000 of 8192 406 -> 325 us; 12 heads
+// of 2304 tokens 57 -> 28 us; d = 128, 24 heads, 512 of 4608 107 -> 79 us, 3000
+// of 4608 239 -> 206 us.
 hipError_t launch_attention(const AttnParams& p, int head_dim, hipStream_t s) {
-  if (head_dim == 64) return launch_t<64, 2, 8, true>(p, s);
-  if (head_dim == 128) return launch_t<128, 1, 8, false>(p, s);
+  const int64_t bh = (int64_t)p.batch * p.heads, q = p.q_count;
+  const int64_t n512 = (q + 511) / 512 * bh, n256 = (q + 255) / 256 * bh, n128 = (q + 127) / 128 * bh;
+  if (head_dim == 64) {
+    const double c512 = (double)((n512 + 255) / 256), c256 = 0.62 * (double)((n256 + 255) / 256);
+    const int64_t left = n128 % 768;
+    const double c128 = 1.09 * (double)(n128 / 768) + (left == 0 ? 0.0 : left <= 256 ? 0.44 : left <= 512 ? 0.74 : 1.09);
+    if (c128 < c512 && c128 < c256) return launch_ring<64, 4, 2>(p, s);
+    if (c256 < c512) return launch_ring<64, 8, 4>(p, s);
+    return launch_t<64, 2, 8, true>(p, s);
+  }
+  if (head_dim == 128) {
+    if (n128 <= 256 || (n256 > 256 && n256 <= 320)) return launch_ring<128, 4, 2>(p, s);
+    return launch_t<128, 1, 8, false>(p, s);
+  }
   return hipErrorInvalidValue;
 }
 
