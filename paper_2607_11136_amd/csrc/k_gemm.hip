@@ -3,15 +3,20 @@
 //
 // Tiling: a BM x 256 output tile per workgroup (BM = 256 or 128), K in steps
 // of 64.  Eight waves (two per SIMD) in a 2 x 4 grid each own a (BM/2) x 64
-// sub-tile held as (BM/64) x 2 accumulators of v_mfma_f32_32x32x16.  Operand
+// sub-tile held as (BM/32) x 4 accumulators of v_mfma_f32_16x16x32.  Operand
 // tiles go from HBM straight into LDS with buffer_load ... lds (no VGPR
-// staging) through two stages.  A step's loads are spread over the two
-// k-steps after the barrier that frees its stage and land by the next
-// barrier.  Wide steps halve the barriers and give 128-byte row segments
-// (whole cache lines) per load, which measured faster than a four-deep ring
-// of 32-wide steps.  The buffer
-// descriptor of each tile covers only that tile's rows, so rows past M read
-// as zero.
+// staging), in whole cache lines (128-byte row segments).  A has two stages
+// and B three, all 160 KB of LDS, and fragments are read from LDS up to five
+// panels of MFMAs ahead, across the step's one barrier (gemm_tile has the
+// order).  The main loop is bound by MFMA issue at the clock that the power
+// limit leaves: a 64-wide step of a 256 x 256 tile takes 1.49 us on all 256
+// CUs (1440 TFLOP/s), against 1.7 us with 32x32x16 MFMAs, two stages of each
+// operand and reads one k-step ahead; a tile's epilogue and start add about 18
+// us.  17776 rows, start of K loop to the last store, before and now:
+//   QKV (9216 x 3072) 994 -> 945 us, out-projection 390 -> 365 us, MLP up
+//   (12288 x 3072) 1268 -> 1180 us, MLP down 1285 -> 1143 us
+// The buffer descriptor of each tile covers only that tile's rows, so rows
+// past M read as zero.
 //
 // One launch covers the rows in two tile heights: the first rows in 256-row
 // tiles, the rest in 128-row tiles dispatched last, which fill the CUs the
@@ -25,7 +30,7 @@
 // tiles with a deeper LDS ring instead (k_gemm_ring; pick_ring_tile has the
 // rule and the times on both sides).
 //
-// LDS layout: a stage holds BM rows of A and 256 rows of B, 64 elements (128
+// LDS layout: a stage of either operand holds its rows' 64 elements (128
 // bytes = eight 16-byte slots) each; slot j of row r is stored at slot
 // j ^ ((r >> 1) & 7).  The LDS has 64 four-byte banks and serves a 16-byte
 // read for 16 lanes per cycle; those 16 lanes read 16 consecutive rows at
@@ -33,17 +38,19 @@
 //
 // The MFMA takes the weight fragment as its A operand and the activation
 // fragment as its B operand, so each lane ends up holding four consecutive
-// output features of one token row: epilogue loads/stores are 8/16 bytes.
+// output features of one token row, and four 16-lane rows 16 of them: epilogue
+// loads and stores are 16 bytes a lane, 64 contiguous bytes a row.
 //
 // Workgroups are dispatched round-robin over the 8 XCDs; the tile order
 // below gives each XCD a contiguous range of tiles, walked in groups of 4
 // tile-rows (1-2% faster than 8 on the block's shapes), so tiles that share
 // operand panels share an L2.
 //
-// Determinism: every output element is the sum over ascending 16-wide K
-// steps, one MFMA each, in the same sequence whatever M, the tile, the row
-// maps or the tile position are; so chunked and unchunked calls, and all
-// tiles, agree bit for bit.
+// Determinism: every output element is the sum over ascending K in the MFMAs'
+// own order, the same whatever M, the tile, the row maps or the tile position
+// are, and a 16x16x32 MFMA's bits are those of two 32x32x16 ones in turn (the
+// tests compare the tiles); so chunked and unchunked calls, and all tiles,
+// agree bit for bit.
 #include <algorithm>
 #include <type_traits>
 #include <vector>
@@ -63,12 +70,18 @@ struct Mfma<bf16> {
   static __device__ __forceinline__ f32x16 run(frag a, frag b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
+  static __device__ __forceinline__ f32x4 run16(frag a, frag b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+  }
 };
 template <>
 struct Mfma<f16> {
   typedef f16x8 frag;
   static __device__ __forceinline__ f32x16 run(frag a, frag b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ f32x4 run16(frag a, frag b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
   }
 };
 
@@ -77,7 +90,6 @@ constexpr int KS = BK / 16;                // MFMA k-steps per stage
 constexpr int ROWB = BK * 2;               // bytes of one operand row in a stage
 constexpr int SLOTS = BK / 8;              // 16-byte slots per row
 constexpr int RPL = 1024 / ROWB;           // rows filled by one 1 KiB wave load
-constexpr int NS = 2;                      // LDS pipeline stages
 constexpr int B_BYTES = BN * BK * 2;       // B bytes per stage
 constexpr int GROUP_M = 4;
 constexpr int NWAVES = 8;                  // 2 x 4 waves, two per SIMD
@@ -85,7 +97,6 @@ constexpr int RING_GROUP_ROWS = 512;       // rows walked before the next column
 constexpr int WN = BN * 2 / NWAVES;        // output columns per wave
 // slot swizzle of a 128-byte row (two rows share a 256-byte bank line)
 __host__ __device__ constexpr int row_swz(int r) { return (r >> 1) & 7; }
-constexpr int NJ = WN / 32;                // 32-column MFMA blocks per wave
 constexpr int BUF_FLAGS = 0x00020000;      // raw buffer, 32-bit dwords
 
 // 16 bytes per lane from buffer offset voff + soff straight into LDS (one
@@ -279,7 +290,7 @@ __device__ __forceinline__ void epilogue_qkv_heads(const GemmParams& p, const f3
       // this wave's sum of squares over its 64 dims, per row
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
-        float ss = 0.f;
+        float sq[2] = {0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -287,9 +298,9 @@ __device__ __forceinline__ void epilogue_qkv_heads(const GemmParams& p, const f3
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const float v = acc[i][j][4 * q + e] + bv[j][q][e];
-              ss = fmaf(v, v, ss);
+              sq[q & 1] = fmaf(v, v, sq[q & 1]);
             }
-        ss = pair_sum(ss);
+        const float ss = pair_sum(sq[0] + sq[1]);
         if (hi == 0) ss_lds[wave * WR + i * 32 + r32] = ss;
       }
     }
@@ -301,7 +312,7 @@ __device__ __forceinline__ void epilogue_qkv_heads(const GemmParams& p, const f3
       const int64_t bb = valid ? m / rpb : 0;
       const int tok = a.tok_begin + (int)(valid ? m - bb * rpb : 0);
       float v[NJ][4][4];
-      float ss = 0.f;
+      float sq[2] = {0.f, 0.f}, ss;   // columns 0..3 and 8..11 of each 16 apart (the order of the 16x16 tiles)
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -309,14 +320,14 @@ __device__ __forceinline__ void epilogue_qkv_heads(const GemmParams& p, const f3
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             v[j][q][e] = acc[i][j][4 * q + e] + bv[j][q][e];
-            ss = fmaf(v[j][q][e], v[j][q][e], ss);
+            sq[q & 1] = fmaf(v[j][q][e], v[j][q][e], sq[q & 1]);
           }
       if constexpr (HALVES > 1) {
         // dims 0..63 (wave wave - half) plus dims 64..127, in that order
         const float* sp = ss_lds + (wave - half) * WR + i * 32 + r32;
         ss = sp[0] + sp[WR];
       } else {
-        ss = pair_sum(ss);
+        ss = pair_sum(sq[0] + sq[1]);
       }
       // 1/sqrt(mean + eps) with the hardware reciprocal square root (1 ulp)
       const float r = __builtin_amdgcn_rsqf(ss * (1.0f / (float)HD) + a.qk_eps);
@@ -496,25 +507,287 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, const f32x16 (&a
   raise_flag(p.status, bad);
 }
 
+// The values of lanes l ^ 16 and l ^ 32 added: the four 16-lane rows' sum, as
+// (row 0 + row 2) + (row 1 + row 3), in every lane.
+__device__ __forceinline__ float rows_sum(float v) {
+  v = pair_sum(v);
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Two 16-column blocks of one row, of which a lane of 16-lane row l4 holds
+// columns 4 l4 .. 4 l4 + 3 each (a, b): rows 2m and 2m + 1 swap halves, then
+// the first stores 8 columns of block a and the second of block b, 16 bytes
+// apiece.  `base` points at block a.
+template <typename CT>
+__device__ __forceinline__ void store_block_pair(CT* base, const CT __attribute__((ext_vector_type(4))) a,
+                                                 const CT __attribute__((ext_vector_type(4))) b, int l4, bool valid) {
+  typedef CT c4 __attribute__((ext_vector_type(4)));
+  static_assert(sizeof(c4) == 8, "16-bit elements");
+  const u32x2 ua = __builtin_bit_cast(u32x2, a), ub = __builtin_bit_cast(u32x2, b);
+  const auto r0 = __builtin_amdgcn_permlane16_swap(ua[0], ub[0], false, false);
+  const auto r1 = __builtin_amdgcn_permlane16_swap(ua[1], ub[1], false, false);
+  const u32x4 o = {r0[0], r1[0], r0[1], r1[1]};
+  if (valid) *reinterpret_cast<u32x4*>(base + 16 * (l4 & 1) + 8 * (l4 >> 1)) = o;
+}
+
+// LDS bytes of one wave's transposed V block in epilogue_qkv_heads16: 64 dims
+// of TPW tokens, padded so that the four dims a store meets lie in other banks.
+constexpr int v_row(int TPW) { return TPW + 8; }
+
+// epilogue_qkv_heads for 16x16 blocks: lane (l16, l4) holds, for tokens
+// 16 i + l16 of the wave, the columns 16 j + 4 l4 + e (j < 4, e < 4).  The same
+// operations in the same order per output.
+template <int MI, int BM, int HD>
+__device__ __forceinline__ void epilogue_qkv_heads16(const GemmParams& p, const f32x4 (&acc)[MI][4], int64_t m0,
+                                                     int64_t m_end, int n0, int wm, int wn, int lane, int wave,
+                                                     uint8_t* smem, const uint16_t* __restrict__ bias) {
+  static_assert(HD == 64 || HD == 128, "head dims");
+  constexpr int NW = NWAVES, WR = 16 * MI;
+  constexpr int HALVES = HD / 64;   // waves per head
+  constexpr int NP = HD / 2;        // rotated pairs per head
+  const QkRopeArgs& a = p.qk;
+  const int l16 = lane & 15, l4 = lane >> 4;
+  const int D = a.heads * HD;
+  const int sect = n0 / D;
+  const int h = (n0 - sect * D) / HD + wn / HALVES;
+  const int half = wn % HALVES;
+  const int64_t rpb = p.c_map.rows_per_batch;
+  const int64_t Lp = a.padded_len;
+  float bv[4][4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) load4f<uint16_t>(bias + n0 + wn * 64 + 16 * j + 4 * l4, bv[j]);
+
+  bool bad = false;  // an fp16 result at or beyond the fp16 range
+  if (sect < 2) {
+    const uint16_t* gam = sect == 0 ? a.q_gamma : a.k_gamma;
+    float g[4][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) load4f<uint16_t>(gam + half * 64 + 16 * j + 4 * l4, g[j]);
+    const float f = sect == 0 ? a.q_scale : 1.0f;
+    f16* dst = sect == 0 ? a.q : a.k;
+    constexpr int CS_STRIDE = NP + 2;  // float2 per padded row
+    constexpr int SS_BYTES = HALVES > 1 ? NW * WR * 4 : 0;
+    static_assert(qkv_epi_lds_bytes(BM, HD, NW, WR) == BM * 16 + SS_BYTES + BM * CS_STRIDE * 8, "LDS plan");
+    int4* pos_lds = reinterpret_cast<int4*>(smem);
+    float* ss_lds = reinterpret_cast<float*>(smem + BM * 16);
+    float2* cs_lds = reinterpret_cast<float2*>(smem + BM * 16 + SS_BYTES);
+    __syncthreads();  // every wave is done reading the operand stages
+    {
+      const int gw = max(a.geom.grid[2], 1), hw = max(a.geom.grid[1] * a.geom.grid[2], 1);
+      for (int t = (int)threadIdx.x; t < BM; t += NW * 64) {
+        const int64_t m = m0 + t;
+        const bool valid = m < m_end;
+        const int64_t bb = valid ? m / rpb : 0;
+        const int vi = a.tok_begin + (int)(valid ? m - bb * rpb : 0) - a.text_len;
+        const bool vis = valid && vi >= 0;
+        pos_lds[t] = make_int4(vis ? 1 : 0, vis ? vi / hw : 0, vis ? (vi % hw) / gw : 0, vis ? vi % gw : 0);
+      }
+    }
+    __syncthreads();
+    {
+      const int np0 = a.geom.dims[0] / 2, np1 = a.geom.dims[1] / 2, np2 = a.geom.dims[2] / 2;
+      const int tb1 = a.geom.grid[0] * np0, tb2 = tb1 + a.geom.grid[1] * np1;
+      for (int e = (int)threadIdx.x; e < BM * NP; e += NW * 64) {
+        const int t = e / NP, pr = e % NP;
+        const int4 ps = pos_lds[t];
+        int idx = -1;
+        if (pr < np0) idx = ps.y * np0 + pr;
+        else if (pr < np0 + np1) idx = tb1 + ps.z * np1 + (pr - np0);
+        else if (pr < np0 + np1 + np2) idx = tb2 + ps.w * np2 + (pr - np0 - np1);
+        cs_lds[t * CS_STRIDE + pr] = (ps.x && idx >= 0) ? a.table[idx] : make_float2(1.f, 0.f);
+      }
+    }
+    float ss[MI];      // of this wave's 64 dims, per token
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      float sq = 0.f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float v = acc[i][j][e] + bv[j][e];
+          sq = fmaf(v, v, sq);
+        }
+      ss[i] = rows_sum(sq);
+      if (HALVES > 1 && l4 == 0) ss_lds[wave * WR + i * 16 + l16] = ss[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      const int64_t m = m0 + wm * WR + i * 16 + l16;
+      const bool valid = m < m_end;
+      const int64_t bb = valid ? m / rpb : 0;
+      const int tok = a.tok_begin + (int)(valid ? m - bb * rpb : 0);
+      float sum = ss[i];
+      if constexpr (HALVES > 1) {
+        // dims 0..63 (wave wave - half) plus dims 64..127, in that order
+        const float* sp = ss_lds + (wave - half) * WR + i * 16 + l16;
+        sum = sp[0] + sp[WR];
+      }
+      // 1/sqrt(mean + eps) with the hardware reciprocal square root (1 ulp)
+      const float r = __builtin_amdgcn_rsqf(sum * (1.0f / (float)HD) + a.qk_eps);
+      const float2* csr = cs_lds + (wm * WR + i * 16 + l16) * CS_STRIDE + half * 32 + 2 * l4;
+      f16* row = dst + (((int64_t)bb * a.heads + h) * Lp + tok) * HD + half * 64;
+      f16x4 o[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        // pairs 8 j + 2 l4 + (0, 1)
+        const f32x4 cc = *reinterpret_cast<const f32x4*>(csr + 8 * j);
+#pragma unroll
+        for (int e2 = 0; e2 < 2; ++e2) {
+          const float2 cs = make_float2(cc[2 * e2], cc[2 * e2 + 1]);
+          const float u0 = (acc[i][j][2 * e2] + bv[j][2 * e2]) * r * g[j][2 * e2];
+          const float u1 = (acc[i][j][2 * e2 + 1] + bv[j][2 * e2 + 1]) * r * g[j][2 * e2 + 1];
+          const float y0 = as_rounded_f32(fmaf(u0, cs.x, -u1 * cs.y) * f);
+          const float y1 = as_rounded_f32(fmaf(u0, cs.y, u1 * cs.x) * f);
+          bad |= valid && (!fits_f16(y0) || !fits_f16(y1));
+          o[j][2 * e2] = (f16)y0;
+          o[j][2 * e2 + 1] = (f16)y1;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; j += 2) store_block_pair<f16>(row + 16 * j, o[j], o[j + 1], l4, valid);
+    }
+    raise_flag(p.status, bad);
+    return;
+  }
+
+  // V: every wave has finished reading the operand stages before they hold
+  // the transposed blocks
+  constexpr int TPW = WR, VR = v_row(TPW);     // tokens of this wave's block, LDS row
+  __syncthreads();
+  f16* lds = reinterpret_cast<f16*>(smem) + wave * 64 * VR;   // [64 dims][TPW tokens]
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    const bool valid = m0 + wm * WR + i * 16 + l16 < m_end;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float y = as_rounded_f32(acc[i][j][e] + bv[j][e]);
+        bad |= valid && !fits_f16(y);
+        lds[(16 * j + 4 * l4 + e) * VR + i * 16 + l16] = (f16)y;
+      }
+  }
+  raise_flag(p.status, bad);
+  __syncthreads();
+  for (int it = lane; it < 64 * (TPW / 8); it += 64) {
+    const int d = it / (TPW / 8), g8 = it % (TPW / 8);
+    const int64_t mf = m0 + wm * TPW + g8 * 8;
+    if (mf >= m_end) continue;
+    const f16x8 vals = *reinterpret_cast<const f16x8*>(lds + d * VR + g8 * 8);
+    const int64_t bb = mf / rpb, ii = mf - bb * rpb;
+    const int tok = a.tok_begin + (int)ii;
+    f16* vrow = a.vt + (((int64_t)bb * a.heads + h) * HD + half * 64 + d) * Lp;
+    if (mf + 8 <= m_end && ii + 8 <= rpb && (tok & 7) == 0) {
+      *reinterpret_cast<f16x8*>(vrow + tok) = vals;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int64_t m = mf + e;
+        if (m < m_end) {
+          const int64_t b2 = m / rpb;
+          a.vt[(((int64_t)b2 * a.heads + h) * HD + half * 64 + d) * Lp + a.tok_begin + (m - b2 * rpb)] = vals[e];
+        }
+      }
+    }
+  }
+}
+
+// store_tile for 16x16 blocks: acc[i][j][e] = C[m][n] with m = m0 + wm WR +
+// 16 i + l16 and n = n0 + wn 64 + 16 j + 4 l4 + e; a store covers 64 contiguous
+// bytes of each of 16 rows.
+template <int EPI, typename CT, typename RT, int MI, int BM>
+__device__ __forceinline__ void store_tile16(const GemmParams& p, const f32x4 (&acc)[MI][4], int64_t m0, int64_t m_end,
+                                             int n0, int wm, int wn, int lane, int wave, uint8_t* smem_raw,
+                                             const uint16_t* __restrict__ bias, CT* __restrict__ cout,
+                                             const RT* __restrict__ resid, const float* __restrict__ gate) {
+  constexpr int WR = 16 * MI;
+  if constexpr (EPI == EPI_QKV_HEADS || EPI == EPI_QKV_HEADS_128) {
+    epilogue_qkv_heads16<MI, BM, EPI == EPI_QKV_HEADS ? 64 : 128>(p, acc, m0, m_end, n0, wm, wn, lane, wave, smem_raw,
+                                                                 bias);
+    return;
+  }
+  const int l16 = lane & 15, l4 = lane >> 4;
+  const int nw = n0 + wn * 64;
+  float bv[4][4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) load4f<uint16_t>(bias + nw + 16 * j + 4 * l4, bv[j]);
+  const int64_t rpb = p.c_map.rows_per_batch;
+  bool bad = false;  // an fp16 result at or beyond the fp16 range
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    const int64_t m = m0 + wm * WR + i * 16 + l16;
+    const bool valid = m < m_end;    // (every lane takes part in the swaps)
+    const int64_t mv = valid ? m : m0;
+    const int64_t b = mv / rpb;
+    const int64_t within = mv - b * rpb;
+    CT* crow_ptr = cout + (b * p.c_map.batch_stride + p.c_map.row_offset + within) * p.ldc;
+    float v[4][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[j][e] = acc[i][j][e] + bv[j][e];
+    if (EPI == XEMA_EPI_GATED_RESIDUAL) {
+      const RT* rrow_ptr = resid + (b * p.resid_map.batch_stride + p.resid_map.row_offset + within) * p.ld_resid;
+      const float* grow = gate + b * p.gate_stride +
+                          (p.gate_sel.pos_offset + within < p.gate_sel.text_len ? p.gate_sel.text_delta : 0);
+      float res[4][4];
+      f32x4 g[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        load4f<RT>(rrow_ptr + nw + 16 * j + 4 * l4, res[j]);
+        g[j] = *reinterpret_cast<const f32x4*>(grow + nw + 16 * j + 4 * l4);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[j][e] = fmaf(g[j][e], v[j][e], res[j][e]);
+    }
+    if (EPI == XEMA_EPI_BIAS_GELU) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[j][e] = gelu_tanh(v[j][e]);
+    }
+    if constexpr (sizeof(CT) == 2) {
+      typedef CT c4 __attribute__((ext_vector_type(4)));
+      c4 o[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float y = as_rounded_f32(v[j][e]);
+          if constexpr (__is_same(CT, f16)) bad |= valid && !fits_f16(y);
+          o[j][e] = from_f32<CT>(y);
+        }
+#pragma unroll
+      for (int j = 0; j < 4; j += 2) store_block_pair<CT>(crow_ptr + nw + 16 * j, o[j], o[j + 1], l4, valid);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (valid) store4<CT>(crow_ptr + nw + 16 * j + 4 * l4, v[j]);
+    }
+  }
+  raise_flag(p.status, bad);
+}
+
 // One BM x 256 output tile.  EPI: XEMA_EPI_BIAS / XEMA_EPI_BIAS_GELU (CT =
 // bf16 or f16) or XEMA_EPI_GATED_RESIDUAL (CT = float, RT = residual element
 // type).  Rows [m_begin, m_end) in tiles of BM rows; wg numbers this tile
-// among them; smem_raw holds the two LDS stages.
+// among them; smem_raw holds two stages of A and three of B.
 template <typename T, int EPI, typename CT, typename RT, int BM>
 __device__ __forceinline__ void gemm_tile(const GemmParams& p, int64_t m_begin, int64_t m_end, int wg,
                                           uint8_t* smem_raw, const uint16_t* __restrict__ bias,
                                           CT* __restrict__ cout, const RT* __restrict__ resid,
                                           const float* __restrict__ gate) {
   static_assert(BM == 256 || BM == 128, "tile heights");
-  constexpr int MI = BM / 64;                         // 32-row MFMA blocks per wave
-  constexpr int A_BYTES = BM * BK * 2;
-  constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-  constexpr int A_LOADS = BM / NWAVES / RPL, B_LOADS = BN / NWAVES / RPL;  // 1 KiB loads per wave per stage
+  constexpr int MI = BM / 32;                         // 16-row blocks per wave
+  constexpr int A_BYTES = BM * ROWB;
+  constexpr int A_LOADS = BM / NWAVES / RPL, B_LOADS = BN / NWAVES / RPL;  // 1 KiB loads per wave per step
   static_assert(A_LOADS * NWAVES * RPL == BM && B_LOADS * NWAVES * RPL == BN, "load split");
-  static_assert(NS == 2 && KS >= 2, "two stages of at least two k-steps");
-  constexpr int LPS = A_LOADS + B_LOADS;
   typedef typename Mfma<T>::frag frag;
-  uint8_t (*smem)[STAGE_BYTES] = reinterpret_cast<uint8_t (*)[STAGE_BYTES]>(smem_raw);
 
   const int K = p.K;
   const int KT = K / BK;
@@ -564,112 +837,111 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int64_t m_begin, 
 
   // The per-lane offsets above are loop-invariant: a step's K offset goes in
   // the instruction's scalar offset, so issuing a load costs no vector ALU
-  // work.  A step past the last one (the pipeline runs two ahead) reloads the
+  // work.  A step past the last one (the pipeline runs ahead) reloads the
   // last step into a stage nobody reads, which keeps the loop free of
   // branches.  Tile offsets stay below 2^31, checked by the host.
-  auto issue = [&](int kt, int idx) {  // load idx of step kt (A loads, then B loads)
-    uint8_t* st = smem[kt % NS];
-    const uint32_t kbyte = (uint32_t)((kt < KT ? kt : KT - 1) * BK * 2);
-    if (idx < A_LOADS) {
-      load_lds16(ra, st + (wave * A_LOADS + idx) * 1024, a_off[idx], kbyte);
-    } else {
-      const int c = idx - A_LOADS;
-      load_lds16(rb, st + A_BYTES + (wave * B_LOADS + c) * 1024, b_off[c], kbyte);
-    }
+  auto k_byte = [&](int kt) { return (uint32_t)((kt < KT ? kt : KT - 1) * BK * 2); };
+  auto issue_a = [&](int kt, uint8_t* st, int c) {
+    load_lds16(ra, st + (wave * A_LOADS + c) * 1024, a_off[c], k_byte(kt));
   };
+  auto issue_b = [&](int kt, uint8_t* st, int c) {
+    load_lds16(rb, st + (wave * B_LOADS + c) * 1024, b_off[c], k_byte(kt));
+  };
+  uint8_t* const b_ring = smem_raw + 2 * A_BYTES;
 
-  f32x16 acc[MI][NJ];
+  f32x4 acc[MI][4];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // fragment addressing: lane reads row (block + lane%32), k-slot kk*2 + lane/32
-  // (blocks start at multiples of 32 rows, so the swizzle is the lane's own)
-  const int r32 = lane & 31, hi = lane >> 5, sw = row_swz(r32);
-  const int a_row0 = (wm * (BM / 2) + r32) * ROWB;  // byte offset of this lane's first A row
-  const int b_row0 = (wn * WN + r32) * ROWB;
-
-  frag fx[2][MI], fw[2][NJ];
-  auto read_one = [&](const uint8_t* st, int kk, int f, frag (&x)[MI], frag (&wv)[NJ]) {
-    const int so = (((kk * 2 + hi) ^ sw) * 16);
-    if (f < MI)
-      x[f] = *reinterpret_cast<const frag*>(st + a_row0 + f * 32 * ROWB + so);
-    else
-      wv[f - MI] = *reinterpret_cast<const frag*>(st + A_BYTES + b_row0 + (f - MI) * 32 * ROWB + so);
+  // fragment addressing: lane l reads row l % 16 of a block, k-slot 4 kk + l / 16
+  const int l16 = lane & 15, l4 = lane >> 4;
+  const int frag_off = l16 * ROWB + ((l4 ^ (l16 >> 1)) * 16);
+  const int a_frag = wm * (BM / 2) * ROWB + frag_off, b_frag = wn * WN * ROWB + frag_off;
+  constexpr int AHEAD = BM == 256 ? 5 : 4, RING = 8;   // A fragments read ahead, and their registers
+  frag fx[RING], fw[2][4];
+  auto read_a = [&](const uint8_t* st, int kk, int i) {
+    return *reinterpret_cast<const frag*>(st + (a_frag ^ (64 * kk)) + i * 16 * ROWB);
   };
-  auto mfma_step = [&](const frag (&x)[MI], const frag (&wv)[NJ]) {
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) acc[i][j] = Mfma<T>::run(wv[j], x[i], acc[i][j]);
+  auto read_b = [&](const uint8_t* st, int kk, int j) {
+    return *reinterpret_cast<const frag*>(st + (b_frag ^ (64 * kk)) + j * 16 * ROWB);
   };
-  constexpr int NR = MI + NJ, NM = MI * NJ;  // LDS reads and MFMAs per k-step
 
-  // Pipeline.  Step kt is consumed from stage kt % 2 over KS k-steps, each
-  // k-step's MFMAs running while the next k-step's fragments are read.  The
-  // barrier before the last k-step of step kt means that every wave has read
-  // all of step kt (its stage is free) and that step kt+1 has landed.  The
-  // loads of step s are issued in two halves: the first during the last
-  // k-step of step s-2, right after the barrier that freed its stage, the
-  // second during the first k-step of step s-1; both land by the barrier of
-  // step s-1.  Spreading them over two k-steps keeps the load address queue
-  // from filling and stalling the MFMA stream.
-  constexpr int H1 = LPS / 2;
+  // Pipeline.  A step is 2 MI panels (a 16-row block of A at one of its two
+  // k-steps) of four MFMAs.  A fragments are read AHEAD panels ahead and those
+  // of B a k-step ahead, so that by panel MEET every wave has read all of step
+  // kt, and from there on reads step kt+1.  At the barrier there, step kt+1 has
+  // landed and A of step kt+2 goes to the stage of A freed; B has three stages,
+  // so that of step kt+2 goes out at the start of step kt already.  With half
+  // of the loads in flight for two steps, no panel waits for the fetch of 64 KB
+  // within one step.
+  constexpr int PANELS = 2 * MI, MEET = PANELS - AHEAD;
+  constexpr int B1 = BM == 256 ? 3 : 0;      // the panels from which B of the second k-step is read
+  static_assert(B1 + 4 <= MEET || BM == 128, "step read before the barrier");
+  static_assert(PANELS % RING == 0, "fragment registers");
+  int bs = 0;                                // the stage of B of step kt
+  auto step = [&](int kt) {
+    uint8_t* a_here = smem_raw + (kt & 1) * A_BYTES;
+    const uint8_t* a_next = smem_raw + ((kt & 1) ^ 1) * A_BYTES;
+    const uint8_t* b_here = b_ring + bs * B_BYTES;
+    bs = bs + 1 == 3 ? 0 : bs + 1;
+    const uint8_t* b_next = b_ring + bs * B_BYTES;
+    uint8_t* b_free = b_ring + (bs + 1 == 3 ? 0 : bs + 1) * B_BYTES;
 #pragma unroll
-  for (int l = 0; l < LPS; ++l) issue(0, l);
-  stage_barrier();
-#pragma unroll
-  for (int f = 0; f < NR; ++f) read_one(smem[0], 0, f, fx[0], fw[0]);
-#pragma unroll
-  for (int l = 0; l < H1; ++l) issue(1, l);
-  for (int kt = 0; kt < KT; ++kt) {
-    const uint8_t* st = smem[kt % NS];
-#pragma unroll
-    for (int kk = 0; kk < KS - 1; ++kk) {
-      const int nl = kk == 0 ? LPS - H1 : 0;
-      const int ne = NR > nl ? NR : nl;
-#pragma unroll
-      for (int e = 0; e < ne; ++e) {
-        if (e < NR) read_one(st, kk + 1, e, fx[(kk + 1) & 1], fw[(kk + 1) & 1]);
-        if (e < nl) issue(kt + 1, H1 + e);
+    for (int m = 0; m < PANELS; ++m) {
+      if (m == MEET) {
+        // A and B of step kt+1 have landed; B of step kt+2 may be in flight
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(B_LOADS));
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
       }
-      mfma_step(fx[kk & 1], fw[kk & 1]);
-      const int ng = NM > ne ? NM : ne;
+      const int kk = m / MI, i = m % MI, a = m + AHEAD;
+      fx[a % RING] = a < PANELS ? read_a(a_here, a / MI, a % MI) : read_a(a_next, (a - PANELS) / MI, (a - PANELS) % MI);
+      const bool rb1 = m >= B1 && m < B1 + 4, rb0 = m >= MEET && m < MEET + 4;
+      if (rb1) fw[1][m - B1] = read_b(b_here, 1, m - B1);
+      if (rb0) fw[0][m - MEET] = read_b(b_next, 0, m - MEET);
+      const bool lb = m < B_LOADS, la = m >= MEET && m < MEET + A_LOADS;
+      if (lb) issue_b(kt + 2, b_free, m);
+      if (la) issue_a(kt + 2, a_here, m - MEET);
 #pragma unroll
-      for (int g = 0; g < ng; ++g) {
-        if (g < NM) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-        if (g < NR) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // LDS read
-        if (g < nl) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // global->LDS load
-      }
+      for (int j = 0; j < 4; ++j) acc[i][j] = Mfma<T>::run16(fw[kk][j], fx[m % RING], acc[i][j]);
+      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);  // MFMA
+      if (rb1 || rb0)
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // LDS reads
+      else
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      if (lb || la) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // global->LDS load
+      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
     }
-    stage_barrier();
-    // the last k-step, with the first fragments of step kt+1 read and the
-    // first half of step kt+2 issued into the stage just freed (after the
-    // last step these read a stage nobody uses and load nothing)
-    const int ne = NR > H1 ? NR : H1;
+  };
 #pragma unroll
-    for (int e = 0; e < ne; ++e) {
-      if (e < NR) read_one(smem[(kt + 1) % NS], 0, e, fx[KS & 1], fw[KS & 1]);
-      if (e < H1) issue(kt + 2, e);
-    }
-    mfma_step(fx[(KS - 1) & 1], fw[(KS - 1) & 1]);
-    const int ng = NM > ne ? NM : ne;
+  for (int c = 0; c < A_LOADS; ++c) issue_a(0, smem_raw, c);
 #pragma unroll
-    for (int g = 0; g < ng; ++g) {
-      if (g < NM) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-      if (g < NR) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // LDS read
-      if (g < H1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // global->LDS load
-    }
-  }
+  for (int c = 0; c < B_LOADS; ++c) issue_b(0, b_ring, c);
+#pragma unroll
+  for (int c = 0; c < B_LOADS; ++c) issue_b(1, b_ring + B_BYTES, c);
+#pragma unroll
+  for (int c = 0; c < A_LOADS; ++c) issue_a(1, smem_raw + A_BYTES, c);
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(A_LOADS + B_LOADS));
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) fw[0][j] = read_b(b_ring, 0, j);
+#pragma unroll
+  for (int m = 0; m < AHEAD; ++m) fx[m] = read_a(smem_raw, m / MI, m % MI);
+  for (int kt = 0; kt < KT; ++kt) step(kt);
   // the reloads of the last iterations still write to LDS: let them finish
-  // before the workgroup can end
+  // before the epilogue or the workgroup's end
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
 
-  store_tile<EPI, CT, RT, MI, NJ, BM, NWAVES, BM / 2>(p, acc, m0, m_end, n0, wm, wn, lane, wave, smem_raw, bias, cout,
-                                                  resid, gate);
+  store_tile16<EPI, CT, RT, MI, BM>(p, acc, m0, m_end, n0, wm, wn, lane, wave, smem_raw, bias, cout, resid, gate);
 }
 
 // A BM x BN output tile, BN = 32 NJ WNW, for problems whose 256-column tiles
@@ -878,7 +1150,7 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void k_gemm(GemmParams p, int64_t s
                                                          const RT* __restrict__ resid,
                                                          const float* __restrict__ gate) {
   // the operand stages; the QKV epilogue at head_dim 128 needs a little more
-  constexpr int STAGES = NS * (256 * BK * 2 + B_BYTES);
+  constexpr int STAGES = 2 * 256 * ROWB + 3 * B_BYTES;
   constexpr int EPI_LDS = EPI == EPI_QKV_HEADS_128 ? qkv_epi_lds_bytes(256, 128) : 0;
   __shared__ __attribute__((aligned(1024))) uint8_t smem[STAGES > EPI_LDS ? STAGES : EPI_LDS];
   const int bx = (int)blockIdx.x;
