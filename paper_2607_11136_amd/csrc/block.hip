@@ -206,8 +206,8 @@ extern "C" int xema_op_convert_f16(const void* src, void* dst, int64_t n, void* 
   if (n % 8) return XEMA_ERR_UNSUPPORTED;
   if (!aligned(src, 16) || !aligned(dst, 16)) return XEMA_ERR_MISALIGNED;
   if (overlaps(src, n * 2, dst, n * 2)) return XEMA_ERR_INVALID_ARG;
-  return hip_status(launch_convert_f16((const uint16_t*)src, (_Float16*)dst, n,
-                                       (hipStream_t)stream));
+  const ConvertF16 c{{(const uint16_t*)src}, {(_Float16*)dst}, {n / 8}};
+  return hip_status(launch_convert_f16(c, (hipStream_t)stream));
 }
 
 // ---------------------------------------------------------------------------
@@ -254,20 +254,26 @@ int run_block(const xema_block_cfg& c, const xema_request& r, const void* tokens
   const int64_t txt_delta = dual_stream(c) ? B * 6 * D : 0;
   auto sel_at = [&](int64_t t0) { return ModSel{t0, r.text_len, txt_delta}; };
 
-  // step 0 (the first launch of a call also clears the range flags)
-  XEMA_TRY(launch_adaln((const uint16_t*)cond, (const uint16_t*)w.ada_w,
-                        (const uint16_t*)w.ada_b, (int)B, (int)Dc, (int)(6 * D), mod, s,
-                        clear_status ? status : nullptr));
-  if (dual_stream(c))
-    XEMA_TRY(launch_adaln((const uint16_t*)cond, (const uint16_t*)w.ada_txt_w,
-                          (const uint16_t*)w.ada_txt_b, (int)B, (int)Dc, (int)(6 * D),
-                          mod + txt_delta, s));
-  XEMA_TRY(launch_rope_table(geom, c.rope_theta, rope, s));
+  // step 0 (which in a call's first block also clears the range flags), and the
+  // zeros of the padding tokens; Q, K and V^T live from step 1 on, and nothing
+  // in the arena dies before that
+  BlockStart st{};
+  st.status = clear_status ? status : nullptr;
+  st.geom = geom; st.theta = c.rope_theta; st.rope = (float2*)rope;
+  st.q = (_Float16*)Q; st.k = (_Float16*)Kk; st.vt = (_Float16*)VT;
+  st.batch = (int)B; st.heads = c.heads; st.head_dim = c.head_dim; st.seq_len = (int)L; st.padded_len = (int)Lp;
+  st.cond = (const uint16_t*)cond; st.cond_dim = (int)Dc; st.out_dim = (int)(6 * D);
+  st.ada_w[0] = (const uint16_t*)w.ada_w; st.ada_b[0] = (const uint16_t*)w.ada_b; st.mod[0] = mod;
+  if (dual_stream(c)) {
+    st.ada_w[1] = (const uint16_t*)w.ada_txt_w; st.ada_b[1] = (const uint16_t*)w.ada_txt_b;
+    st.mod[1] = mod + txt_delta;
+  }
+  XEMA_TRY(launch_block_start(st, s));
 
   // phase A: LN1 -> QKV -> QK-norm/RoPE scatter, per token chunk.  The QKV
   // GEMM's epilogue does the scatter itself (a head per wave at head dim 64,
   // per two waves at 128; the shape checks admit only these), so the qkv
-  // slot stays empty; the padding tokens are zeroed once.
+  // slot stays empty; the padding tokens were zeroed above.
   for (int64_t t0 = 0; t0 < L; t0 += ch) {
     const int64_t cc = std::min(ch, L - t0);
     const RowMap xmap{cc, L, t0};
@@ -283,14 +289,12 @@ int run_block(const xema_block_cfg& c, const xema_request& r, const void* tokens
     g.status = status + 0;
     XEMA_TRY(launch_gemm(g, s));
   }
-  XEMA_TRY(launch_qkv_pad(qk_args(c, r, qkv, 0, 0, w.q_gamma, w.k_gamma, rope, Q, Kk, VT),
-                          c.head_dim, (int)L, s));
-
   // step 4: fp16 copies of the phase-B weights, unless the caller passed them
   if (copy_w) {
-    XEMA_TRY(launch_convert_f16((const uint16_t*)w.o_w, (_Float16*)wo16, D * D, s, status + 3));
-    XEMA_TRY(launch_convert_f16((const uint16_t*)w.up_w, (_Float16*)wup16, F * D, s, status + 3));
-    XEMA_TRY(launch_convert_f16((const uint16_t*)w.down_w, (_Float16*)wdown16, D * F, s, status + 3));
+    const ConvertF16 cv{{(const uint16_t*)w.o_w, (const uint16_t*)w.up_w, (const uint16_t*)w.down_w},
+                        {(_Float16*)wo16, (_Float16*)wup16, (_Float16*)wdown16},
+                        {D * D / 8, F * D / 8, D * F / 8}};
+    XEMA_TRY(launch_convert_f16(cv, s, status + 3));
   }
 
   // phase B: attention -> out-proj -> LN2 -> MLP, per query chunk

@@ -16,17 +16,9 @@ namespace xema {
 // a0: mod[b][n] = sum_k w[n][k] cond[b][k] + bias[n].  One wave per output row
 // n; each lane reads 16-byte slices of the row; up to 8 batch rows per pass.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_adaln(const uint16_t* __restrict__ cond,
-                                               const uint16_t* __restrict__ w,
-                                               const uint16_t* __restrict__ bias, int batch,
-                                               int cond_dim, int out_dim,
-                                               float* __restrict__ mod,
-                                               uint32_t* __restrict__ status_clear) {
-  const int lane = threadIdx.x & 63;
-  const int64_t n = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  // the block's range flags start clear (the first launch of every call)
-  if (status_clear != nullptr && blockIdx.x == 0 && threadIdx.x < XEMA_STATUS_WORDS)
-    status_clear[threadIdx.x] = 0u;
+__device__ __forceinline__ void adaln_row(const uint16_t* __restrict__ cond, const uint16_t* __restrict__ w,
+                                          const uint16_t* __restrict__ bias, int batch, int cond_dim, int out_dim,
+                                          float* __restrict__ mod, int64_t n, int lane) {
   if (n >= out_dim) return;
   const uint16_t* wrow = w + n * cond_dim;
   const float bn = bf16_bits_to_f32(bias[n]);
@@ -75,6 +67,13 @@ __global__ __launch_bounds__(256) void k_adaln(const uint16_t* __restrict__ cond
       }
     }
   }
+}
+
+__global__ __launch_bounds__(256) void k_adaln(const uint16_t* __restrict__ cond, const uint16_t* __restrict__ w,
+                                               const uint16_t* __restrict__ bias, int batch, int cond_dim,
+                                               int out_dim, float* __restrict__ mod) {
+  adaln_row(cond, w, bias, batch, cond_dim, out_dim, mod, (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6),
+            threadIdx.x & 63);
 }
 
 // ---------------------------------------------------------------------------
@@ -199,8 +198,7 @@ __global__ __launch_bounds__(256) void k_ln_modulate(const XT* __restrict__ x, R
 // Step 0: RoPE table.  Entry (axis a, position p, pair j) = (cos, sin) of
 // p * theta^(-2j/d_a), computed in fp64.
 // ---------------------------------------------------------------------------
-__global__ void k_rope_table(RopeGeom g, float theta, float2* __restrict__ table) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void rope_entry(const RopeGeom& g, float theta, float2* __restrict__ table, int i) {
   int base = 0;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
@@ -215,6 +213,58 @@ __global__ void k_rope_table(RopeGeom g, float theta, float2* __restrict__ table
     }
     base += n;
   }
+}
+
+__global__ void k_rope_table(RopeGeom g, float theta, float2* __restrict__ table) {
+  rope_entry(g, theta, table, blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+static int rope_entries(const RopeGeom& g) {
+  int n = 0;
+  for (int a = 0; a < 3; ++a) n += g.grid[a] * (g.dims[a] / 2);
+  return n;
+}
+
+// ---------------------------------------------------------------------------
+// Everything a block needs before its first LayerNorm, in one launch: the
+// range flags cleared, the RoPE table, zeros for the padding tokens [L, Lp) of
+// Q, K ([B, H, Lp, d]) and V^T ([B, H, d, Lp]), which the QKV GEMM does not
+// write, and the AdaLN map (two for a dual-stream block).  None depends on
+// another; as launches of their own the first three cost a 288-token block 8 us
+// of its 58 beside their gaps, all of it latency (the fp64 angles, a few
+// scattered stores).  The short blocks come first in dispatch order.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void k_block_start(BlockStart a, int rope_blocks, int pad_blocks, int map_blocks) {
+  if (blockIdx.x == 0 && a.status != nullptr && threadIdx.x < XEMA_STATUS_WORDS) a.status[threadIdx.x] = 0u;
+  int bx = (int)blockIdx.x;
+  if (bx < rope_blocks) {
+    rope_entry(a.geom, a.theta, a.rope, bx * 256 + (int)threadIdx.x);
+    return;
+  }
+  bx -= rope_blocks;
+  if (bx < pad_blocks) {    // one (batch row, head)
+    const int64_t Lp = a.padded_len, hb = bx;
+    const int pad = (int)(Lp - a.seq_len), n = pad * a.head_dim, shift = a.head_dim == 64 ? 6 : 7;
+    for (int i = threadIdx.x; i < n; i += 256) {
+      const int64_t at = (hb * Lp + a.seq_len) * a.head_dim + i;   // the padding rows are contiguous
+      a.q[at] = (f16)0.f;
+      a.k[at] = (f16)0.f;
+      a.vt[((hb << shift) + i / pad) * Lp + a.seq_len + i % pad] = (f16)0.f;
+    }
+    return;
+  }
+  bx -= pad_blocks;
+  const int m = bx >= map_blocks;
+  adaln_row(a.cond, a.ada_w[m], a.ada_b[m], a.batch, a.cond_dim, a.out_dim, a.mod[m],
+            (int64_t)(bx - m * map_blocks) * 4 + (threadIdx.x >> 6), threadIdx.x & 63);
+}
+
+hipError_t launch_block_start(const BlockStart& a, hipStream_t s) {
+  const int rope = (rope_entries(a.geom) + 255) / 256;
+  const int pad = a.padded_len > a.seq_len ? a.batch * a.heads : 0;
+  const int map = (a.out_dim + 3) / 4, maps = a.ada_w[1] ? 2 : 1;
+  hipLaunchKernelGGL(k_block_start, dim3((unsigned)(rope + pad + maps * map)), dim3(256), 0, s, a, rope, pad, map);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -365,15 +415,25 @@ __global__ __launch_bounds__(256) void k_qk_norm_rope(QkRopeArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Step 4: bf16 -> fp16 copy, 8 elements per thread per iteration.
+// Step 4: bf16 -> fp16 copies, 8 elements per thread per iteration, of up to
+// three tensors in one launch (a block's W_o, W_up and W_down: three launches
+// of a 288-token block took 7 us, one 3).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_convert_f16(const uint16_t* __restrict__ src,
-                                                     f16* __restrict__ dst, int64_t n8,
-                                                     uint32_t* __restrict__ status) {
+__global__ __launch_bounds__(256) void k_convert_f16(ConvertF16 c, uint32_t* __restrict__ status) {
   bool bad = false;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n8;
-       i += (int64_t)gridDim.x * 256) {
-    const u32x4 u = reinterpret_cast<const u32x4*>(src)[i];
+  const int64_t n = c.n8[0] + c.n8[1] + c.n8[2];
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    int64_t j = i;
+    const uint16_t* src = c.src[0];
+    _Float16* dst = c.dst[0];
+    if (j >= c.n8[0]) {
+      j -= c.n8[0];
+      const bool third = j >= c.n8[1];
+      if (third) j -= c.n8[1];
+      src = third ? c.src[2] : c.src[1];
+      dst = third ? c.dst[2] : c.dst[1];
+    }
+    const u32x4 u = reinterpret_cast<const u32x4*>(src)[j];
     f16x8 o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -382,7 +442,7 @@ __global__ __launch_bounds__(256) void k_convert_f16(const uint16_t* __restrict_
       o[2 * e] = (f16)w0;
       o[2 * e + 1] = (f16)w1;
     }
-    reinterpret_cast<f16x8*>(dst)[i] = o;
+    reinterpret_cast<f16x8*>(dst)[j] = o;
   }
   raise_flag(status, bad);
 }
@@ -391,9 +451,9 @@ __global__ __launch_bounds__(256) void k_convert_f16(const uint16_t* __restrict_
 // Launchers
 // ---------------------------------------------------------------------------
 hipError_t launch_adaln(const uint16_t* cond, const uint16_t* w, const uint16_t* bias, int batch,
-                        int cond_dim, int out_dim, float* mod, hipStream_t s, uint32_t* status_clear) {
+                        int cond_dim, int out_dim, float* mod, hipStream_t s) {
   hipLaunchKernelGGL(k_adaln, dim3((out_dim + 3) / 4), dim3(256), 0, s, cond, w, bias, batch,
-                     cond_dim, out_dim, mod, status_clear);
+                     cond_dim, out_dim, mod);
   return hipGetLastError();
 }
 
@@ -461,41 +521,10 @@ hipError_t launch_ln_modulate(const void* x, int x_dtype, RowMap m, int64_t rows
 }
 
 hipError_t launch_rope_table(RopeGeom g, float theta, float* table, hipStream_t s) {
-  int n = 0;
-  for (int a = 0; a < 3; ++a) n += g.grid[a] * (g.dims[a] / 2);
+  const int n = rope_entries(g);
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_rope_table, dim3((n + 255) / 256), dim3(256), 0, s, g, theta,
                      (float2*)table);
-  return hipGetLastError();
-}
-
-// Zeros for the padding tokens [L, Lp) of Q and K ([B, H, Lp, d]) and V^T
-// ([B, H, d, Lp]) when the QKV GEMM writes the heads itself; one workgroup
-// per (head, batch row).
-template <int HD>
-__global__ __launch_bounds__(256) void k_qkv_pad(QkRopeArgs a, int seq_len) {
-  const int h = blockIdx.x, b = blockIdx.y;
-  const int64_t Lp = a.padded_len;
-  const int64_t hb = (int64_t)b * a.heads + h;
-  const int n = (int)(Lp - seq_len) * HD;
-  for (int i = threadIdx.x; i < n; i += 256) {
-    const int64_t t = seq_len + i / HD;
-    const int d = i % HD;
-    a.q[(hb * Lp + t) * HD + d] = (f16)0.f;
-    a.k[(hb * Lp + t) * HD + d] = (f16)0.f;
-    a.vt[(hb * HD + d) * Lp + t] = (f16)0.f;
-  }
-}
-
-hipError_t launch_qkv_pad(const QkRopeArgs& a, int head_dim, int seq_len, hipStream_t s) {
-  if (a.padded_len <= seq_len || a.heads <= 0 || a.batch <= 0) return hipSuccess;
-  const dim3 grid((unsigned)a.heads, (unsigned)a.batch);
-  if (head_dim == 64)
-    hipLaunchKernelGGL(k_qkv_pad<64>, grid, dim3(256), 0, s, a, seq_len);
-  else if (head_dim == 128)
-    hipLaunchKernelGGL(k_qkv_pad<128>, grid, dim3(256), 0, s, a, seq_len);
-  else
-    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
@@ -510,11 +539,11 @@ hipError_t launch_qk_norm_rope(const QkRopeArgs& a, int head_dim, hipStream_t s)
   return hipGetLastError();
 }
 
-hipError_t launch_convert_f16(const uint16_t* src, f16* dst, int64_t n, hipStream_t s, uint32_t* status) {
-  const int64_t n8 = n / 8;
+hipError_t launch_convert_f16(const ConvertF16& c, hipStream_t s, uint32_t* status) {
+  const int64_t n8 = c.n8[0] + c.n8[1] + c.n8[2];
   const int64_t blocks = std::min<int64_t>((n8 + 255) / 256, 256 * 16);
   if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_convert_f16, dim3((unsigned)blocks), dim3(256), 0, s, src, dst, n8, status);
+  hipLaunchKernelGGL(k_convert_f16, dim3((unsigned)blocks), dim3(256), 0, s, c, status);
   return hipGetLastError();
 }
 

@@ -84,10 +84,22 @@ struct UpconvParams {
 hipError_t launch_upconv_prep(const uint16_t* w, int ci, int co, uint16_t* wp, hipStream_t s);
 hipError_t launch_upconv(const UpconvParams& p, hipStream_t s);
 
-// status_clear (may be null): XEMA_STATUS_WORDS range flags zeroed by the launch.
+// What a block computes before its first LayerNorm (one launch).
+struct BlockStart {
+  uint32_t* status;            // XEMA_STATUS_WORDS range flags to clear (may be null)
+  RopeGeom geom;
+  float theta;
+  float2* rope;
+  _Float16 *q, *k, *vt;        // [B, H, Lp, d], [B, H, d, Lp]: zeros for the tokens [seq_len, padded_len)
+  int batch, heads, head_dim, seq_len, padded_len;
+  const uint16_t* cond;        // [batch, cond_dim]
+  const uint16_t *ada_w[2], *ada_b[2];   // the AdaLN map(s); the second may be null
+  float* mod[2];
+  int cond_dim, out_dim;
+};
+hipError_t launch_block_start(const BlockStart& a, hipStream_t s);
 hipError_t launch_adaln(const uint16_t* cond, const uint16_t* w, const uint16_t* bias, int batch,
-                        int cond_dim, int out_dim, float* mod, hipStream_t s,
-                        uint32_t* status_clear = nullptr);
+                        int cond_dim, int out_dim, float* mod, hipStream_t s);
 // status (may be null): set when an fp16 output leaves the fp16 range.
 hipError_t launch_ln_modulate(const void* x, int x_dtype, RowMap m, int64_t rows, int dim,
                               const float* shift, const float* scale, int64_t mod_stride,
@@ -95,11 +107,13 @@ hipError_t launch_ln_modulate(const void* x, int x_dtype, RowMap m, int64_t rows
                               uint32_t* status = nullptr);
 hipError_t launch_rope_table(RopeGeom g, float theta, float* table, hipStream_t s);
 hipError_t launch_qk_norm_rope(const QkRopeArgs& a, int head_dim, hipStream_t s);
-// Zeros for the padding tokens [L, Lp) of Q, K and V^T (all batch rows, heads).
-hipError_t launch_qkv_pad(const QkRopeArgs& a, int head_dim, int seq_len, hipStream_t s);
 // status (may be null): set when a converted value leaves the fp16 range.
-hipError_t launch_convert_f16(const uint16_t* src, _Float16* dst, int64_t n, hipStream_t s,
-                              uint32_t* status = nullptr);
+struct ConvertF16 {
+  const uint16_t* src[3];
+  _Float16* dst[3];
+  int64_t n8[3];               // elements / 8; 0: no tensor
+};
+hipError_t launch_convert_f16(const ConvertF16& c, hipStream_t s, uint32_t* status = nullptr);
 hipError_t launch_gemm(const GemmParams& p, hipStream_t s);
 
 }  // namespace xema
