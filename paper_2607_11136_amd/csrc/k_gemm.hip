@@ -94,7 +94,6 @@ constexpr int B_BYTES = BN * BK * 2;       // B bytes per stage
 constexpr int GROUP_M = 4;
 constexpr int NWAVES = 8;                  // 2 x 4 waves, two per SIMD
 constexpr int RING_GROUP_ROWS = 512;       // rows walked before the next columns (k_gemm_ring)
-constexpr int WN = BN * 2 / NWAVES;        // output columns per wave
 // slot swizzle of a 128-byte row (two rows share a 256-byte bank line)
 __host__ __device__ constexpr int row_swz(int r) { return (r >> 1) & 7; }
 constexpr int BUF_FLAGS = 0x00020000;      // raw buffer, 32-bit dwords
@@ -696,10 +695,10 @@ __device__ __forceinline__ void epilogue_qkv_heads16(const GemmParams& p, const 
 }
 
 // store_tile for 16x16 blocks: acc[i][j][e] = C[m][n] with m = m0 + wm WR +
-// 16 i + l16 and n = n0 + wn 64 + 16 j + 4 l4 + e; a store covers 64 contiguous
+// 16 i + l16 and n = n0 + 16 NJ wn + 16 j + 4 l4 + e; a store covers 64 contiguous
 // bytes of each of 16 rows.
-template <int EPI, typename CT, typename RT, int MI, int BM>
-__device__ __forceinline__ void store_tile16(const GemmParams& p, const f32x4 (&acc)[MI][4], int64_t m0, int64_t m_end,
+template <int EPI, typename CT, typename RT, int MI, int NJ, int BM>
+__device__ __forceinline__ void store_tile16(const GemmParams& p, const f32x4 (&acc)[MI][NJ], int64_t m0, int64_t m_end,
                                              int n0, int wm, int wn, int lane, int wave, uint8_t* smem_raw,
                                              const uint16_t* __restrict__ bias, CT* __restrict__ cout,
                                              const RT* __restrict__ resid, const float* __restrict__ gate) {
@@ -710,10 +709,10 @@ __device__ __forceinline__ void store_tile16(const GemmParams& p, const f32x4 (&
     return;
   }
   const int l16 = lane & 15, l4 = lane >> 4;
-  const int nw = n0 + wn * 64;
-  float bv[4][4];
+  const int nw = n0 + wn * 16 * NJ;
+  float bv[NJ][4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) load4f<uint16_t>(bias + nw + 16 * j + 4 * l4, bv[j]);
+  for (int j = 0; j < NJ; ++j) load4f<uint16_t>(bias + nw + 16 * j + 4 * l4, bv[j]);
   const int64_t rpb = p.c_map.rows_per_batch;
   bool bad = false;  // an fp16 result at or beyond the fp16 range
 #pragma unroll
@@ -724,38 +723,38 @@ __device__ __forceinline__ void store_tile16(const GemmParams& p, const f32x4 (&
     const int64_t b = mv / rpb;
     const int64_t within = mv - b * rpb;
     CT* crow_ptr = cout + (b * p.c_map.batch_stride + p.c_map.row_offset + within) * p.ldc;
-    float v[4][4];
+    float v[NJ][4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[j][e] = acc[i][j][e] + bv[j][e];
     if (EPI == XEMA_EPI_GATED_RESIDUAL) {
       const RT* rrow_ptr = resid + (b * p.resid_map.batch_stride + p.resid_map.row_offset + within) * p.ld_resid;
       const float* grow = gate + b * p.gate_stride +
                           (p.gate_sel.pos_offset + within < p.gate_sel.text_len ? p.gate_sel.text_delta : 0);
-      float res[4][4];
-      f32x4 g[4];
+      float res[NJ][4];
+      f32x4 g[NJ];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < NJ; ++j) {
         load4f<RT>(rrow_ptr + nw + 16 * j + 4 * l4, res[j]);
         g[j] = *reinterpret_cast<const f32x4*>(grow + nw + 16 * j + 4 * l4);
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[j][e] = fmaf(g[j][e], v[j][e], res[j][e]);
     }
     if (EPI == XEMA_EPI_BIAS_GELU) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[j][e] = gelu_tanh(v[j][e]);
     }
     if constexpr (sizeof(CT) == 2) {
       typedef CT c4 __attribute__((ext_vector_type(4)));
-      c4 o[4];
+      c4 o[NJ];
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float y = as_rounded_f32(v[j][e]);
@@ -763,36 +762,37 @@ __device__ __forceinline__ void store_tile16(const GemmParams& p, const f32x4 (&
           o[j][e] = from_f32<CT>(y);
         }
 #pragma unroll
-      for (int j = 0; j < 4; j += 2) store_block_pair<CT>(crow_ptr + nw + 16 * j, o[j], o[j + 1], l4, valid);
+      for (int j = 0; j < NJ; j += 2) store_block_pair<CT>(crow_ptr + nw + 16 * j, o[j], o[j + 1], l4, valid);
     } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < NJ; ++j)
         if (valid) store4<CT>(crow_ptr + nw + 16 * j + 4 * l4, v[j]);
     }
   }
   raise_flag(p.status, bad);
 }
 
-// One BM x 256 output tile.  EPI: XEMA_EPI_BIAS / XEMA_EPI_BIAS_GELU (CT =
+// One BM x BN_ output tile, in WMW x 8 / WMW waves of 16 MI x 16 NJ.  EPI: XEMA_EPI_BIAS / XEMA_EPI_BIAS_GELU (CT =
 // bf16 or f16) or XEMA_EPI_GATED_RESIDUAL (CT = float, RT = residual element
 // type).  Rows [m_begin, m_end) in tiles of BM rows; wg numbers this tile
 // among them; smem_raw holds two stages of A and three of B.
-template <typename T, int EPI, typename CT, typename RT, int BM>
+template <typename T, int EPI, typename CT, typename RT, int BM, int BN_ = BN, int WMW = 2>
 __device__ __forceinline__ void gemm_tile(const GemmParams& p, int64_t m_begin, int64_t m_end, int wg,
                                           uint8_t* smem_raw, const uint16_t* __restrict__ bias,
                                           CT* __restrict__ cout, const RT* __restrict__ resid,
                                           const float* __restrict__ gate) {
   static_assert(BM == 256 || BM == 128, "tile heights");
-  constexpr int MI = BM / 32;                         // 16-row blocks per wave
-  constexpr int A_BYTES = BM * ROWB;
-  constexpr int A_LOADS = BM / NWAVES / RPL, B_LOADS = BN / NWAVES / RPL;  // 1 KiB loads per wave per step
-  static_assert(A_LOADS * NWAVES * RPL == BM && B_LOADS * NWAVES * RPL == BN, "load split");
+  constexpr int WNW = NWAVES / WMW, WR = BM / WMW, WCOLS = BN_ / WNW;
+  constexpr int MI = WR / 16, NJ = WCOLS / 16;        // 16-row and 16-column blocks per wave
+  constexpr int A_BYTES = BM * ROWB, B_BYTES = BN_ * ROWB;
+  constexpr int A_LOADS = BM / NWAVES / RPL, B_LOADS = BN_ / NWAVES / RPL;  // 1 KiB loads per wave per step
+  static_assert(A_LOADS * NWAVES * RPL == BM && B_LOADS * NWAVES * RPL == BN_ && NJ % 2 == 0, "load split");
   typedef typename Mfma<T>::frag frag;
 
   const int K = p.K;
   const int KT = K / BK;
   const int tiles_m = (int)((m_end - m_begin + BM - 1) / BM);
-  const int tiles_n = p.N / BN;
+  const int tiles_n = p.N / BN_;
   const int total = tiles_m * tiles_n;
   // XCD-aware tile order (see the file comment)
   const int xcd = wg & 7, slot = wg >> 3;
@@ -805,16 +805,16 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int64_t m_begin, 
   const int tm = first_m + in_group % gsize;
   const int tn = in_group / gsize;
   const int64_t m0 = m_begin + (int64_t)tm * BM;
-  const int n0 = tn * BN;
+  const int n0 = tn * BN_;
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wave / (BN / WN), wn = wave % (BN / WN);
+  const int wm = wave / WNW, wn = wave % WNW;
 
   const T* A = reinterpret_cast<const T*>(p.a);
   const T* Bw = reinterpret_cast<const T*>(p.b);
   const int64_t rows_a = min<int64_t>(BM, m_end - m0);
   const __amdgpu_buffer_rsrc_t ra = make_rsrc(A + m0 * K, rows_a * K * 2);
-  const __amdgpu_buffer_rsrc_t rb = make_rsrc(Bw + (int64_t)n0 * K, (int64_t)BN * K * 2);
+  const __amdgpu_buffer_rsrc_t rb = make_rsrc(Bw + (int64_t)n0 * K, (int64_t)BN_ * K * 2);
 
   // Direct-to-LDS load plan: a 1 KiB wave instruction fills RPL rows; wave w
   // fills A rows (BM/NWAVES) w .. and B rows (BN/NWAVES) w ..  Lane l writes
@@ -849,18 +849,18 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int64_t m_begin, 
   };
   uint8_t* const b_ring = smem_raw + 2 * A_BYTES;
 
-  f32x4 acc[MI][4];
+  f32x4 acc[MI][NJ];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // fragment addressing: lane l reads row l % 16 of a block, k-slot 4 kk + l / 16
   const int l16 = lane & 15, l4 = lane >> 4;
   const int frag_off = l16 * ROWB + ((l4 ^ (l16 >> 1)) * 16);
-  const int a_frag = wm * (BM / 2) * ROWB + frag_off, b_frag = wn * WN * ROWB + frag_off;
-  constexpr int AHEAD = BM == 256 ? 5 : 4, RING = 8;   // A fragments read ahead, and their registers
-  frag fx[RING], fw[2][4];
+  const int a_frag = wm * WR * ROWB + frag_off, b_frag = wn * WCOLS * ROWB + frag_off;
+  constexpr int AHEAD = MI == 8 ? 5 : 4, RING = 8;   // A fragments read ahead, and their registers
+  frag fx[RING], fw[2][NJ];
   auto read_a = [&](const uint8_t* st, int kk, int i) {
     return *reinterpret_cast<const frag*>(st + (a_frag ^ (64 * kk)) + i * 16 * ROWB);
   };
@@ -869,7 +869,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int64_t m_begin, 
   };
 
   // Pipeline.  A step is 2 MI panels (a 16-row block of A at one of its two
-  // k-steps) of four MFMAs.  A fragments are read AHEAD panels ahead and those
+  // k-steps) of NJ MFMAs.  A fragments are read AHEAD panels ahead and those
   // of B a k-step ahead, so that by panel MEET every wave has read all of step
   // kt, and from there on reads step kt+1.  At the barrier there, step kt+1 has
   // landed and A of step kt+2 goes to the stage of A freed; B has three stages,
@@ -877,8 +877,8 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int64_t m_begin, 
   // of the loads in flight for two steps, no panel waits for the fetch of 64 KB
   // within one step.
   constexpr int PANELS = 2 * MI, MEET = PANELS - AHEAD;
-  constexpr int B1 = BM == 256 ? 3 : 0;      // the panels from which B of the second k-step is read
-  static_assert(B1 + 4 <= MEET || BM == 128, "step read before the barrier");
+  constexpr int B1 = MI == 8 ? 3 : 0;        // the panel from which B of the second k-step is read, over four
+  static_assert(B1 + 4 <= MEET && MEET + 4 <= PANELS && B_LOADS <= MEET, "step read before the barrier");
   static_assert(PANELS % RING == 0, "fragment registers");
   int bs = 0;                                // the stage of B of step kt
   auto step = [&](int kt) {
@@ -902,20 +902,26 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int64_t m_begin, 
       const int kk = m / MI, i = m % MI, a = m + AHEAD;
       fx[a % RING] = a < PANELS ? read_a(a_here, a / MI, a % MI) : read_a(a_next, (a - PANELS) / MI, (a - PANELS) % MI);
       const bool rb1 = m >= B1 && m < B1 + 4, rb0 = m >= MEET && m < MEET + 4;
-      if (rb1) fw[1][m - B1] = read_b(b_here, 1, m - B1);
-      if (rb0) fw[0][m - MEET] = read_b(b_next, 0, m - MEET);
+      const int nb = rb1 ? m - B1 : m - MEET, j0 = nb * NJ / 4, j1 = (nb + 1) * NJ / 4;
+#pragma unroll
+      for (int j = j0; j < j1; ++j) {
+        if (rb1) fw[1][j] = read_b(b_here, 1, j);
+        if (rb0) fw[0][j] = read_b(b_next, 0, j);
+      }
       const bool lb = m < B_LOADS, la = m >= MEET && m < MEET + A_LOADS;
       if (lb) issue_b(kt + 2, b_free, m);
       if (la) issue_a(kt + 2, a_here, m - MEET);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = Mfma<T>::run16(fw[kk][j], fx[m % RING], acc[i][j]);
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);  // MFMA
-      if (rb1 || rb0)
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // LDS reads
+      for (int j = 0; j < NJ; ++j) acc[i][j] = Mfma<T>::run16(fw[kk][j], fx[m % RING], acc[i][j]);
+      __builtin_amdgcn_sched_group_barrier(0x008, NJ / 2, 0);  // MFMA
+      if ((rb1 || rb0) && j1 - j0 == 2)
+        __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);  // LDS reads
+      else if (rb1 || rb0)
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
       else
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       if (lb || la) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // global->LDS load
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, NJ / 2, 0);
     }
   };
 #pragma unroll
@@ -933,7 +939,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int64_t m_begin, 
   asm volatile("" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) fw[0][j] = read_b(b_ring, 0, j);
+  for (int j = 0; j < NJ; ++j) fw[0][j] = read_b(b_ring, 0, j);
 #pragma unroll
   for (int m = 0; m < AHEAD; ++m) fx[m] = read_a(smem_raw, m / MI, m % MI);
   for (int kt = 0; kt < KT; ++kt) step(kt);
@@ -941,7 +947,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int64_t m_begin, 
   // before the epilogue or the workgroup's end
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
 
-  store_tile16<EPI, CT, RT, MI, BM>(p, acc, m0, m_end, n0, wm, wn, lane, wave, smem_raw, bias, cout, resid, gate);
+  store_tile16<EPI, CT, RT, MI, NJ, BM>(p, acc, m0, m_end, n0, wm, wn, lane, wave, smem_raw, bias, cout, resid, gate);
 }
 
 // A BM x BN output tile, BN = 32 NJ WNW, for problems whose 256-column tiles
@@ -1135,6 +1141,18 @@ __global__ __launch_bounds__(WMW * WNW * 64, 1) void k_gemm_ring(GemmParams p, c
   gemm_ring_tile<T, EPI, CT, RT, BM, WMW, WNW, NJ_, NS_>(p, (int)blockIdx.x, smem, bias, cout, resid, gate);
 }
 
+// 256 x 192 tiles with the pipeline of gemm_tile (4 x 2 waves of 64 x 96):
+// 1000 x 12288 x 3072 75.8 -> 68.1 us, 2048 x 12288 x 3072 155 -> 138 us, 4000 x
+// 3072 x 3072 83.7 -> 75.3 us against the two-stage ring of 32x32x16 MFMAs that
+// these tiles had (1.3 us a step in place of 1.45).
+template <typename T, int EPI, typename CT, typename RT>
+__global__ __launch_bounds__(NWAVES * 64, 1) void k_gemm_192(GemmParams p, const uint16_t* __restrict__ bias,
+                                                             CT* __restrict__ cout, const RT* __restrict__ resid,
+                                                             const float* __restrict__ gate) {
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * 256 * ROWB + 3 * 192 * ROWB];
+  gemm_tile<T, EPI, CT, RT, 256, 192, 4>(p, 0, p.M, (int)blockIdx.x, smem, bias, cout, resid, gate);
+}
+
 // One launch, two tile heights: 256-row tiles of rows [0, split) and
 // 128-row tiles of rows [split, M).  The first `first_small` workgroups take
 // half-height tiles, the next tiles_big the full tiles, the rest the other
@@ -1207,36 +1225,42 @@ static int64_t gemm_row_split(int64_t M, int tiles_n, double* rounds) {
   return best_split;
 }
 
-// The tiles of k_gemm_ring, with the microseconds one 64-wide K step of a tile
-// takes when the 256 CUs hold about one each (measured at K = 3072 and 12288;
-// a CU fetches about 55 GB/s from beyond its L2, so the small tiles cost their
-// operand bytes and only the 256-row ones their MFMAs).  A problem whose
+// The tiles of k_gemm_192 and k_gemm_ring, with the microseconds one 64-wide K
+// step of a tile takes when the 256 CUs hold about one each (measured at K =
+// 3072 and 12288; a CU fetches about 55 GB/s from beyond its L2, so the small
+// tiles cost their operand bytes and only the 256-row ones their MFMAs), and for
+// the tiles of 16x16 MFMAs the part of a tile's time that does not grow with K
+// (fitted to 8192 x 3072 at K = 3072, where two rounds of 256 x 192 win by 8%,
+// and 8000 x 3072 at K = 12288, where they lose by 8%).  A problem whose
 // 256 x 256 tiles do not fill a few rounds of the CUs takes the tile with the
 // fewest rounds x step cost; measured against the 256-column tiles alone:
 //   512 x 3072 x 3072     64 x 128    50 -> 20 us
 //   1000 x 3072 x 12288   128 x 96   232 -> 106 us
 //   2048 x 3072 x 12288   128 x 192  241 -> 158 us
-//   2048 x 12288 x 3072   256 x 192  187 -> 154 us
+//   2048 x 12288 x 3072   256 x 192  187 -> 138 us
+//   4000 x 3072 x 3072    256 x 192   96 -> 75 us
 //   256 x 3072 x 12288    64 x 64    159 -> 46 us
 //   4608 x 3072 x 3072    256 x 256  105 us (128 x 192: 128, 256 x 128: 113)
 enum RingTile { R256x192, R256x128, R128x192, R128x128, R128x96, R64x128, R64x64, N_RING_TILES };
-struct RingCost { int rows, cols; double step_us; };
-static const RingCost kRingCost[N_RING_TILES] = {
-    {256, 192, 1.45}, {256, 128, 1.0}, {128, 192, 0.8}, {128, 128, 0.6}, {128, 96, 0.52}, {64, 128, 0.38}, {64, 64, 0.25}};
-constexpr double FULL_STEP_US = 1.7;  // of the 256 x 256 tile
+struct RingCost { int rows, cols; double step_us, tile_us; };
+static const RingCost kRingCost[N_RING_TILES] = {{256, 192, 1.27, 1.5}, {256, 128, 1.0, 0}, {128, 192, 0.8, 0},
+                                                 {128, 128, 0.6, 0},   {128, 96, 0.52, 0}, {64, 128, 0.38, 0},
+                                                 {64, 64, 0.25, 0}};
+constexpr double FULL_STEP_US = 1.58, FULL_TILE_US = 6;  // of the 256 x 256 tile
 
 // The ring tile for an M x N problem, or -1 for the 256-column tiles (whose
 // modelled time is `rounds` full tiles).  heads_dim: 64 or 128 for the QKV
 // epilogue, which needs 64 columns a wave and, at 128, two waves a row.
-static int pick_ring_tile(int64_t M, int N, double rounds, int heads_dim) {
+static int pick_ring_tile(int64_t M, int N, int K, double rounds, int heads_dim) {
   int best = -1;
-  double cost = 0.95 * rounds * FULL_STEP_US;  // a modelled gain below 5% is none
+  const double steps = K / BK;
+  double cost = 0.95 * rounds * (FULL_STEP_US * steps + FULL_TILE_US);  // a modelled gain below 5% is none
   for (int t = 0; t < N_RING_TILES; ++t) {
     const RingCost& c = kRingCost[t];
     if (N % c.cols) continue;
     if (heads_dim && c.cols != 128 && !(heads_dim == 64 && t == R64x64)) continue;
     const int64_t tiles = ((M + c.rows - 1) / c.rows) * (N / c.cols);
-    const double us = (double)((tiles + 255) / 256) * c.step_us;
+    const double us = (double)((tiles + 255) / 256) * (c.step_us * steps + c.tile_us);
     if (us < cost - 1e-9) { cost = us; best = t; }
   }
   return best;
@@ -1256,7 +1280,7 @@ static hipError_t launch_t(const GemmParams& p, hipStream_t s) {
   double rounds;
   const int64_t split = gemm_row_split(p.M, tiles_n, &rounds);
   constexpr int HD = EPI == EPI_QKV_HEADS ? 64 : EPI == EPI_QKV_HEADS_128 ? 128 : 0;
-  switch (pick_ring_tile(p.M, p.N, rounds, HD)) {
+  switch (pick_ring_tile(p.M, p.N, p.K, rounds, HD)) {
     case R256x128: return launch_ring<T, EPI, CT, RT, 256, 4, 2, 2, 3>(p, s);
     case R128x128: return launch_ring<T, EPI, CT, RT, 128, 2, 2, 2, 4>(p, s);
     case R64x128: return launch_ring<T, EPI, CT, RT, 64, 2, 2, 2, 3>(p, s);
@@ -1264,7 +1288,12 @@ static hipError_t launch_t(const GemmParams& p, hipStream_t s) {
       if constexpr (HD != 128) return launch_ring<T, EPI, CT, RT, 64, 2, 1, 2, 4>(p, s);
       break;
     case R256x192:
-      if constexpr (HD == 0) return launch_ring<T, EPI, CT, RT, 256, 4, 2, 3, 2>(p, s);
+      if constexpr (HD == 0) {
+        const int64_t tiles = (p.M + 255) / 256 * (p.N / 192);
+        hipLaunchKernelGGL((k_gemm_192<T, EPI, CT, RT>), dim3((unsigned)tiles), dim3(NWAVES * 64), 0, s, p, p.bias,
+                           (CT*)p.c, (const RT*)p.resid, p.gate);
+        return hipGetLastError();
+      }
       break;
     case R128x192:
       if constexpr (HD == 0) return launch_ring<T, EPI, CT, RT, 128, 2, 2, 3, 3>(p, s);
