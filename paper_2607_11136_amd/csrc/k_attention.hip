@@ -31,6 +31,8 @@
 //     within a tile, so that MFMAs of one are issued beside the
 //     exponentials of the other.  Scores must stay below 2^16 in log2 units.
 // Measured on the workloads' own Q/K/V, each is the faster one at its width.
+// k_attention_ring takes the launches that would leave CUs idle, with the
+// per-column arithmetic of the kernel for its width (launch_attention has the rule).
 //
 // Keys are visited in one fixed ascending order of 64-key tiles, and every
 // operation is per query column (a wave takes the rescaling path when any of
@@ -44,7 +46,7 @@
 // bank conflicts.  Tiles are filled with buffer_load ... lds, 1 KiB per wave
 // instruction.
 //
-// Workgroups: NW = 8 waves = 8 * QB * 32 queries of one (batch, head).  The
+// Workgroups: NW = 8 (or 4) waves = NW * QB * 32 queries of one (batch, head).  The
 // grid is 1-D and remapped so that all query blocks of a head run on one XCD
 // and share its L2 copy of K and V.
 #include <type_traits>

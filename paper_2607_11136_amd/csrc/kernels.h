@@ -74,7 +74,7 @@ constexpr int EPI_QKV_HEADS_128 = 4;
 // The VAE decoder's fused upsampling stage (k_upconv.hip).
 struct UpconvParams {
   const uint16_t* x;     // bf16 [n, h, w, ci]
-  const uint16_t* wp;    // bf16 phase-summed weights [4][co][4][ci]
+  const uint16_t* wp;    // bf16 phase-summed weights [4][co][8][ci] (4 hi, 4 lo)
   const uint16_t* bias;  // bf16 [co]
   uint16_t* y;           // bf16 [n, 2h, 2w, co]
   int n, h, w, ci, co;
