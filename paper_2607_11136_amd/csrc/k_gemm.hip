@@ -289,7 +289,7 @@ __device__ __forceinline__ void epilogue_qkv_heads(const GemmParams& p, const f3
       // this wave's sum of squares over its 64 dims, per row
 #pragma unroll
       for (int i = 0; i < MI; ++i) {
-        float sq[2] = {0.f, 0.f};
+        float ss = 0.f;
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -297,9 +297,9 @@ __device__ __forceinline__ void epilogue_qkv_heads(const GemmParams& p, const f3
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const float v = acc[i][j][4 * q + e] + bv[j][q][e];
-              sq[q & 1] = fmaf(v, v, sq[q & 1]);
+              ss = fmaf(v, v, ss);
             }
-        const float ss = pair_sum(sq[0] + sq[1]);
+        ss = pair_sum(ss);
         if (hi == 0) ss_lds[wave * WR + i * 32 + r32] = ss;
       }
     }
@@ -311,7 +311,7 @@ __device__ __forceinline__ void epilogue_qkv_heads(const GemmParams& p, const f3
       const int64_t bb = valid ? m / rpb : 0;
       const int tok = a.tok_begin + (int)(valid ? m - bb * rpb : 0);
       float v[NJ][4][4];
-      float sq[2] = {0.f, 0.f}, ss;   // columns 0..3 and 8..11 of each 16 apart (the order of the 16x16 tiles)
+      float ss = 0.f;
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -319,14 +319,14 @@ __device__ __forceinline__ void epilogue_qkv_heads(const GemmParams& p, const f3
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             v[j][q][e] = acc[i][j][4 * q + e] + bv[j][q][e];
-            sq[q & 1] = fmaf(v[j][q][e], v[j][q][e], sq[q & 1]);
+            ss = fmaf(v[j][q][e], v[j][q][e], ss);
           }
       if constexpr (HALVES > 1) {
         // dims 0..63 (wave wave - half) plus dims 64..127, in that order
         const float* sp = ss_lds + (wave - half) * WR + i * 32 + r32;
         ss = sp[0] + sp[WR];
       } else {
-        ss = pair_sum(sq[0] + sq[1]);
+        ss = pair_sum(ss);
       }
       // 1/sqrt(mean + eps) with the hardware reciprocal square root (1 ulp)
       const float r = __builtin_amdgcn_rsqf(ss * (1.0f / (float)HD) + a.qk_eps);
@@ -506,14 +506,6 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, const f32x16 (&a
   raise_flag(p.status, bad);
 }
 
-// The values of lanes l ^ 16 and l ^ 32 added: the four 16-lane rows' sum, as
-// (row 0 + row 2) + (row 1 + row 3), in every lane.
-__device__ __forceinline__ float rows_sum(float v) {
-  v = pair_sum(v);
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
 // Two 16-column blocks of one row, of which a lane of 16-lane row l4 holds
 // columns 4 l4 .. 4 l4 + 3 each (a, b): rows 2m and 2m + 1 swap halves, then
 // the first stores 8 columns of block a and the second of block b, 16 bytes
@@ -597,19 +589,40 @@ __device__ __forceinline__ void epilogue_qkv_heads16(const GemmParams& p, const 
         cs_lds[t * CS_STRIDE + pr] = (ps.x && idx >= 0) ? a.table[idx] : make_float2(1.f, 0.f);
       }
     }
-    float ss[MI];      // of this wave's 64 dims, per token
+    // The sums of squares over this wave's 64 dims, per token, in the order of
+    // epilogue_qkv_heads: columns 0..3 and 8..11 of each 16 in one chain, the
+    // others in a second, then both added.  The lanes of 16-lane rows l4 and l4 + 2
+    // hold the parts of one chain for two tokens; they trade halves, so that the
+    // first has the whole chain of token block i and the second that of i + 1.
+    float ss[MI];
+    static_assert(MI % 2 == 0, "token blocks in pairs");
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
+    for (int i = 0; i < MI; i += 2) {
       float sq = 0.f;
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < 4; ++j) {
+        float v0[4], v1[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float v = acc[i][j][e] + bv[j][e];
-          sq = fmaf(v, v, sq);
+          const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[i][j][e] + bv[j][e]),
+                                                          __float_as_uint(acc[i + 1][j][e] + bv[j][e]), false, false);
+          v0[e] = __uint_as_float(r[0]);
+          v1[e] = __uint_as_float(r[1]);
         }
-      ss[i] = rows_sum(sq);
-      if (HALVES > 1 && l4 == 0) ss_lds[wave * WR + i * 16 + l16] = ss[i];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sq = fmaf(v0[e], v0[e], sq);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sq = fmaf(v1[e], v1[e], sq);
+      }
+      const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(sq), __float_as_uint(sq), false, false);
+      const uint32_t both = __float_as_uint(__uint_as_float(r16[0]) + __uint_as_float(r16[1]));
+      const auto r32 = __builtin_amdgcn_permlane32_swap(both, both, false, false);
+      ss[i] = __uint_as_float(r32[0]);
+      ss[i + 1] = __uint_as_float(r32[1]);
+      if (HALVES > 1 && l4 == 0) {
+        ss_lds[wave * WR + i * 16 + l16] = ss[i];
+        ss_lds[wave * WR + (i + 1) * 16 + l16] = ss[i + 1];
+      }
     }
     __syncthreads();
 #pragma unroll
