@@ -17,8 +17,7 @@
  * directly: the upsampled image U (as large as y) is never stored, and each
  * output phase (parity of u and v) is a 2x2 convolution of x with weights
  * summed over the 3x3 taps that land on the same source pixel, each kept as
- * two bf16 values, hi + lo.  Nine of the sixteen sums give all four phases
- * from products of neighbouring pixels, added in fp32: 14/36 of the
+ * two bf16 values, hi + lo (a single tap needs no lo): 28/36 of the
  * convolution's multiply-adds.  A call may cover a band of source rows, so a
  * caller can produce the output in row bands (chunking); the bytes of every
  * band equal those of the whole-image call.

@@ -1,0 +1,34 @@
+"""The launchers' tile rules (csrc/tile_rules.h) compiled for the host, so that
+tests can say which tile a size takes."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2607_11136_amd", "csrc")
+
+SHIM = r"""
+#include "tile_rules.h"
+using namespace xema;
+extern "C" {
+int upconv_count() { return kNumUpconvTiles; }
+int upconv(int n, int h, int w, int ci, int co, int row_begin, int row_count) {
+  return upconv_pick(UpconvSize{n, h, w, ci, co, row_begin, row_count});
+}
+}
+"""
+
+
+@functools.lru_cache(None)
+def lib() -> ctypes.CDLL:
+    with tempfile.TemporaryDirectory(prefix="tile_rules_") as d:
+        src, so = os.path.join(d, "shim.cpp"), os.path.join(d, "shim.so")
+        with open(src, "w") as f:
+            f.write(SHIM)
+        subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I" + CSRC, src, "-o", so], check=True)
+        return ctypes.CDLL(so)
+
+
+def upconv(n, h, w, ci, co, row_begin=0, row_count=None) -> int:
+    return lib().upconv(n, h, w, ci, co, row_begin, h if row_count is None else row_count)
