@@ -20,15 +20,14 @@
 //
 // One launch covers the rows in two tile heights: the first rows in 256-row
 // tiles, the rest in 128-row tiles dispatched last, which fill the CUs the
-// last round of full tiles leaves idle.  The launcher picks the split from a
-// model of the completion time (e.g. 17776 x 3072 is 840 tiles of 256 x 256,
-// four rounds over 256 CUs with the last 28% full; 54 tile-rows of 256 and 31
-// of 128 finish in about 3.6 rounds).
+// last round of full tiles leaves idle.  The split comes from a model of the
+// completion time (gemm_row_split in tile_rules.h; e.g. 17776 x 3072 is 840 tiles
+// of 256 x 256, four rounds over 256 CUs with the last 28% full; 54 tile-rows of
+// 256 and 31 of 128 finish in about 3.6 rounds).
 //
 // Problems that these tiles would not spread over the CUs (chunks of a few
 // hundred to a few thousand tokens, narrow layers) take smaller or narrower
-// tiles with a deeper LDS ring instead (k_gemm_ring; pick_ring_tile has the
-// rule and the times on both sides).
+// tiles with a deeper LDS ring instead (k_gemm_ring; gemm_pick has the rule).
 //
 // LDS layout: a stage of either operand holds its rows' 64 elements (128
 // bytes = eight 16-byte slots) each; slot j of row r is stored at slot
@@ -53,10 +52,10 @@
 // agree bit for bit.
 #include <algorithm>
 #include <type_traits>
-#include <vector>
 
 #include "device_common.h"
 #include "kernels.h"
+#include "tile_rules.h"
 
 namespace xema {
 
@@ -825,9 +824,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int64_t m_begin, 
 
   const T* A = reinterpret_cast<const T*>(p.a);
   const T* Bw = reinterpret_cast<const T*>(p.b);
-  const int64_t rows_a = min<int64_t>(BM, m_end - m0);
-  const __amdgpu_buffer_rsrc_t ra = make_rsrc(A + m0 * K, rows_a * K * 2);
-  const __amdgpu_buffer_rsrc_t rb = make_rsrc(Bw + (int64_t)n0 * K, (int64_t)BN_ * K * 2);
+  const int64_t bytes_a = min<int64_t>(BM, m_end - m0) * K * 2, bytes_b = (int64_t)BN_ * K * 2;
 
   // Direct-to-LDS load plan: a 1 KiB wave instruction fills RPL rows; wave w
   // fills A rows (BM/NWAVES) w .. and B rows (BN/NWAVES) w ..  Lane l writes
@@ -850,15 +847,16 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int64_t m_begin, 
 
   // The per-lane offsets above are loop-invariant: a step's K offset goes in
   // the instruction's scalar offset, so issuing a load costs no vector ALU
-  // work.  A step past the last one (the pipeline runs ahead) reloads the
-  // last step into a stage nobody reads, which keeps the loop free of
-  // branches.  Tile offsets stay below 2^31, checked by the host.
-  auto k_byte = [&](int kt) { return (uint32_t)((kt < KT ? kt : KT - 1) * BK * 2); };
+  // work.  A step past the last one (the pipeline runs ahead) goes to a stage
+  // nobody reads, from a buffer of no bytes, which keeps the loop free of branches
+  // and fetches nothing.  Tile offsets stay below 2^31, checked by the host.
   auto issue_a = [&](int kt, uint8_t* st, int c) {
-    load_lds16(ra, st + (wave * A_LOADS + c) * 1024, a_off[c], k_byte(kt));
+    load_lds16(make_rsrc(A + m0 * K, kt < KT ? bytes_a : 0), st + (wave * A_LOADS + c) * 1024, a_off[c],
+               (uint32_t)(kt * BK * 2));
   };
   auto issue_b = [&](int kt, uint8_t* st, int c) {
-    load_lds16(rb, st + (wave * B_LOADS + c) * 1024, b_off[c], k_byte(kt));
+    load_lds16(make_rsrc(Bw + (int64_t)n0 * K, kt < KT ? bytes_b : 0), st + (wave * B_LOADS + c) * 1024, b_off[c],
+               (uint32_t)(kt * BK * 2));
   };
   uint8_t* const b_ring = smem_raw + 2 * A_BYTES;
 
@@ -956,7 +954,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int64_t m_begin, 
 #pragma unroll
   for (int m = 0; m < AHEAD; ++m) fx[m] = read_a(smem_raw, m / MI, m % MI);
   for (int kt = 0; kt < KT; ++kt) step(kt);
-  // the reloads of the last iterations still write to LDS: let them finish
+  // the loads of the last iterations still write to LDS: let them finish
   // before the epilogue or the workgroup's end
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
 
@@ -1193,92 +1191,6 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void k_gemm(GemmParams p, int64_t s
     gemm_tile<T, EPI, CT, RT, 128>(p, split, p.M, bx - tiles_big, smem, bias, cout, resid, gate);
 }
 
-// Completion time of n_big full tiles, then n_small half-height tiles costing
-// `half` of a full one, dealt in order to the first free of 256 CUs (tiles
-// freed at the same time form one group).
-static double tile_makespan(int64_t n_big, int64_t n_small, double half) {
-  constexpr int64_t CUS = 256;
-  const int64_t rounds = n_big / CUS, extra = n_big % CUS;
-  std::vector<std::pair<double, int64_t>> free_at;  // (time, CUs)
-  if (CUS - extra) free_at.push_back({(double)rounds, CUS - extra});
-  if (extra) free_at.push_back({(double)rounds + 1.0, extra});
-  double end = free_at.back().first;
-  if (n_big == 0) end = 0.0;
-  while (n_small > 0) {
-    size_t i = 0;
-    for (size_t j = 1; j < free_at.size(); ++j)
-      if (free_at[j].first < free_at[i].first) i = j;
-    const double t = free_at[i].first;
-    const int64_t k = std::min(free_at[i].second, n_small);
-    n_small -= k;
-    end = std::max(end, t + half);
-    if (free_at[i].second == k) free_at.erase(free_at.begin() + i);
-    else free_at[i].second -= k;
-    bool merged = false;
-    for (auto& g : free_at)
-      if (g.first == t + half) { g.second += k; merged = true; }
-    if (!merged) free_at.push_back({t + half, k});
-  }
-  return end;
-}
-
-// Rows [0, split) go to 256-row tiles, the rest to 128-row tiles: the split
-// with the least modelled completion time, a half-height tile costing 0.62 of
-// a full one (measured).  *rounds receives that time in full tiles.
-static int64_t gemm_row_split(int64_t M, int tiles_n, double* rounds) {
-  const int64_t tm = (M + 255) / 256;
-  int64_t best_split = M;
-  double best = tile_makespan(tm * tiles_n, 0, 0.62);
-  for (int64_t t1 = tm - 1; t1 >= 0 && t1 >= tm - 16; --t1) {
-    const int64_t rest = (M - t1 * 256 + 127) / 128;
-    const double cost = tile_makespan(t1 * tiles_n, rest * tiles_n, 0.62);
-    if (cost < best - 1e-9) { best = cost; best_split = t1 * 256; }
-  }
-  *rounds = best;
-  return best_split;
-}
-
-// The tiles of k_gemm_192 and k_gemm_ring, with the microseconds one 64-wide K
-// step of a tile takes when the 256 CUs hold about one each (measured at K =
-// 3072 and 12288; a CU fetches about 55 GB/s from beyond its L2, so the small
-// tiles cost their operand bytes and only the 256-row ones their MFMAs), and for
-// the tiles of 16x16 MFMAs the part of a tile's time that does not grow with K
-// (fitted to 8192 x 3072 at K = 3072, where two rounds of 256 x 192 win by 8%,
-// and 8000 x 3072 at K = 12288, where they lose by 8%).  A problem whose
-// 256 x 256 tiles do not fill a few rounds of the CUs takes the tile with the
-// fewest rounds x step cost; measured against the 256-column tiles alone:
-//   512 x 3072 x 3072     64 x 128    50 -> 20 us
-//   1000 x 3072 x 12288   128 x 96   232 -> 106 us
-//   2048 x 3072 x 12288   128 x 192  241 -> 158 us
-//   2048 x 12288 x 3072   256 x 192  187 -> 138 us
-//   4000 x 3072 x 3072    256 x 192   96 -> 75 us
-//   256 x 3072 x 12288    64 x 64    159 -> 46 us
-//   4608 x 3072 x 3072    256 x 256  105 us (128 x 192: 128, 256 x 128: 113)
-enum RingTile { R256x192, R256x128, R128x192, R128x128, R128x96, R64x128, R64x64, N_RING_TILES };
-struct RingCost { int rows, cols; double step_us, tile_us; };
-static const RingCost kRingCost[N_RING_TILES] = {{256, 192, 1.27, 1.5}, {256, 128, 1.0, 0}, {128, 192, 0.8, 0},
-                                                 {128, 128, 0.6, 0},   {128, 96, 0.52, 0}, {64, 128, 0.38, 0},
-                                                 {64, 64, 0.25, 0}};
-constexpr double FULL_STEP_US = 1.58, FULL_TILE_US = 6;  // of the 256 x 256 tile
-
-// The ring tile for an M x N problem, or -1 for the 256-column tiles (whose
-// modelled time is `rounds` full tiles).  heads_dim: 64 or 128 for the QKV
-// epilogue, which needs 64 columns a wave and, at 128, two waves a row.
-static int pick_ring_tile(int64_t M, int N, int K, double rounds, int heads_dim) {
-  int best = -1;
-  const double steps = K / BK;
-  double cost = 0.95 * rounds * (FULL_STEP_US * steps + FULL_TILE_US);  // a modelled gain below 5% is none
-  for (int t = 0; t < N_RING_TILES; ++t) {
-    const RingCost& c = kRingCost[t];
-    if (N % c.cols) continue;
-    if (heads_dim && c.cols != 128 && !(heads_dim == 64 && t == R64x64)) continue;
-    const int64_t tiles = ((M + c.rows - 1) / c.rows) * (N / c.cols);
-    const double us = (double)((tiles + 255) / 256) * (c.step_us * steps + c.tile_us);
-    if (us < cost - 1e-9) { cost = us; best = t; }
-  }
-  return best;
-}
-
 template <typename T, int EPI, typename CT, typename RT, int BM, int WMW, int WNW, int NJ_, int NS_>
 static hipError_t launch_ring(const GemmParams& p, hipStream_t s) {
   const int64_t tiles = ((p.M + BM - 1) / BM) * (p.N / (WNW * 32 * NJ_));
@@ -1290,17 +1202,17 @@ static hipError_t launch_ring(const GemmParams& p, hipStream_t s) {
 template <typename T, int EPI, typename CT, typename RT>
 static hipError_t launch_t(const GemmParams& p, hipStream_t s) {
   const int tiles_n = p.N / BN;
-  double rounds;
-  const int64_t split = gemm_row_split(p.M, tiles_n, &rounds);
   constexpr int HD = EPI == EPI_QKV_HEADS ? 64 : EPI == EPI_QKV_HEADS_128 ? 128 : 0;
-  switch (pick_ring_tile(p.M, p.N, p.K, rounds, HD)) {
-    case R256x128: return launch_ring<T, EPI, CT, RT, 256, 4, 2, 2, 3>(p, s);
-    case R128x128: return launch_ring<T, EPI, CT, RT, 128, 2, 2, 2, 4>(p, s);
-    case R64x128: return launch_ring<T, EPI, CT, RT, 64, 2, 2, 2, 3>(p, s);
-    case R64x64:
+  const GemmPick pick = gemm_pick(p.M, p.N, p.K, HD);
+  const int64_t split = pick.split;
+  switch (pick.tile) {
+    case G256x128: return launch_ring<T, EPI, CT, RT, 256, 4, 2, 2, 3>(p, s);
+    case G128x128: return launch_ring<T, EPI, CT, RT, 128, 2, 2, 2, 4>(p, s);
+    case G64x128: return launch_ring<T, EPI, CT, RT, 64, 2, 2, 2, 3>(p, s);
+    case G64x64:
       if constexpr (HD != 128) return launch_ring<T, EPI, CT, RT, 64, 2, 1, 2, 4>(p, s);
       break;
-    case R256x192:
+    case G256x192:
       if constexpr (HD == 0) {
         const int64_t tiles = (p.M + 255) / 256 * (p.N / 192);
         hipLaunchKernelGGL((k_gemm_192<T, EPI, CT, RT>), dim3((unsigned)tiles), dim3(NWAVES * 64), 0, s, p, p.bias,
@@ -1308,25 +1220,26 @@ static hipError_t launch_t(const GemmParams& p, hipStream_t s) {
         return hipGetLastError();
       }
       break;
-    case R128x192:
+    case G128x192:
       if constexpr (HD == 0) return launch_ring<T, EPI, CT, RT, 128, 2, 2, 3, 3>(p, s);
       break;
-    case R128x96:
+    case G128x96:
       if constexpr (HD == 0) return launch_ring<T, EPI, CT, RT, 128, 4, 1, 3, 4>(p, s);
       break;
     default: break;
   }
   const int64_t big = ((split + 255) / 256) * tiles_n;
   const int64_t small = ((p.M - split + 127) / 128) * tiles_n;
-  // Up to 192 half-height tiles first (a multiple of 8, so that each set of
+  // Up to 96 half-height tiles first (a multiple of 8, so that each set of
   // tiles keeps its XCD-aware order) for the gated-residual epilogue at
   // short K (the out-projection), whose epilogue is a large share of a tile.
-  // Measured against none first: 17776 x 3072 x 3072 5% faster, 18432 rows
-  // 3.5%, 106306 rows 2%, 57224 x 4096 x 4096 unchanged; at K = 12288 and
-  // with the other epilogues no faster.  The dispatch order changes no
+  // Measured with none, 96 and 192 first, us: 17776 x 3072 x 3072 343, 328, 330;
+  // 18432 rows 347, 330, 339; 9216 x 4096 x 4096 297, 285, 286; 13000 x 3072 x
+  // 1024 128, 119, 124; 57224 x 4096 x 4096 the same; at K = 12288 1074, 1101, 1091,
+  // and with the other epilogues no faster.  The dispatch order changes no
   // result: every tile sums its K products in the same order.
   const int first_small =
-      (EPI == XEMA_EPI_GATED_RESIDUAL && p.K <= 4096) ? (int)(std::min<int64_t>(small, 192) & ~7) : 0;
+      (EPI == XEMA_EPI_GATED_RESIDUAL && p.K <= 4096) ? (int)(std::min<int64_t>(small, 96) & ~7) : 0;
   hipLaunchKernelGGL((k_gemm<T, EPI, CT, RT>), dim3((unsigned)(big + small)), dim3(NWAVES * 64), 0, s, p,
                      split, (int)big, first_small, p.bias, (CT*)p.c, (const RT*)p.resid, p.gate);
   return hipGetLastError();
