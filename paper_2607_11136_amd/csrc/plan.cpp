@@ -121,6 +121,8 @@ int layout_for_chunk(const xema_block_cfg& cfg, const xema_request& req, int64_t
   const bool chunked = c < L;
   const int64_t copies = cfg.weights_f16 ? 0 : 1;  // fp16 weight copies made by the call
   struct Spec { int64_t bytes; int begin, end; };
+  // Q, K and V^T hold values from step 1 on, but the block's first launch (step 0)
+  // already zeroes their padding tokens: no slot may end at step 1.
   const Spec spec[XEMA_NUM_SLOTS] = {
       {24 * B * D * (dual_stream(cfg) ? 2 : 1), 0, 10},  // XEMA_SLOT_MOD
       {rope_table_bytes(cfg, req), 0, 4},          // XEMA_SLOT_ROPE

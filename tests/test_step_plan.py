@@ -184,7 +184,8 @@ SLOT = {n: i for i, n in enumerate(LY.SLOT_NAMES)}
 def _replay(s, n, g, c):
     """Live instances (buffer, first write, last read) of every buffer the
     step's workspace holds, in the order the step runs its operations:
-    blocks, then groups of g sequences, then phase A per chunk (LN1; QKV
+    blocks, then groups of g sequences, then the start (which also zeroes the
+    padding tokens of Q, K, V^T), phase A per chunk (LN1; QKV
     writing Q, K, V^T) and phase B per chunk (attention; out-projection
     reading the block's input; LN2; MLP up; MLP down writing the block's
     output).  A buffer rewritten per group or per chunk starts a new
@@ -204,8 +205,7 @@ def _replay(s, n, g, c):
         x_in = out_key(i - 1) if i > 0 else None
         for _ in range(B // g):
             t += 1
-            start = t                                   # AdaLN map, RoPE table, status clear
-            qkv_start = None
+            start = t                                   # AdaLN map, RoPE table, status clear, Q, K, V^T's padding
             for _ in chunks:
                 t += 1
                 ln1 = t                                 # LN1 reads the input, writes ln1
@@ -213,7 +213,6 @@ def _replay(s, n, g, c):
                     resid_last[x_in] = t
                 t += 1                                  # QKV reads ln1, writes Q, K, V^T
                 spans.append((("slot", i, SLOT["ln1"]), ln1, t))
-                qkv_start = qkv_start or t
             spans.append((("slot", i, SLOT["rope"]), start, t))
             t += 1
             copies = t                                  # the fp16 weight copies
@@ -237,7 +236,7 @@ def _replay(s, n, g, c):
                 if out_key(i):
                     resid_first.setdefault(out_key(i), t)
             for name in ("q", "k", "vt"):
-                spans.append((("slot", i, SLOT[name]), qkv_start, qkv_end))
+                spans.append((("slot", i, SLOT[name]), start, qkv_end))
             for name in ("wo16", "wup16", "wdown16"):
                 spans.append((("slot", i, SLOT[name]), copies, t))
             for name in ("mod", "status"):
