@@ -11,10 +11,11 @@
 // order).  The main loop is bound by MFMA issue at the clock that the power
 // limit leaves: a 64-wide step of a 256 x 256 tile takes 1.49 us on all 256
 // CUs (1440 TFLOP/s), against 1.7 us with 32x32x16 MFMAs, two stages of each
-// operand and reads one k-step ahead; a tile's epilogue and start add about 18
-// us.  17776 rows, start of K loop to the last store, before and now:
-//   QKV (9216 x 3072) 994 -> 945 us, out-projection 390 -> 365 us, MLP up
-//   (12288 x 3072) 1268 -> 1180 us, MLP down 1285 -> 1143 us
+// operand and reads one k-step ahead.  With all CUs at it a tile takes 7.6 us
+// besides with 16-bit stores, 10 with GELU and 30 with the gated residual
+// (20480 x 12288 at K = 64 to 1024).  The video block's launches, kernel trace:
+//   QKV (17776 x 9216 x 3072) 858 -> 856 us, out-projection 364 -> 334 us, MLP up
+//   (12288 x 3072) 1144 -> 1083 us, MLP down 1248 -> 1080 us
 // The buffer descriptor of each tile covers only that tile's rows, so rows
 // past M read as zero.
 //
@@ -166,22 +167,9 @@ __device__ __forceinline__ void load4f<uint16_t>(const uint16_t* p, float v[4]) 
   v[3] = __uint_as_float(u[1] & 0xffff0000u);
 }
 
-// Workgroup barrier of the main loop: wait for every LDS-bound load and LDS
-// access of this wave, then s_barrier.  The empty asm statements keep the
-// compiler from moving LDS accesses across; the scheduling fences keep the
-// MFMAs of each k-step on their side of the barrier.
 // s_waitcnt immediate: vmcnt[3:0] in bits 3:0 and vmcnt[5:4] in bits 15:14,
 // expcnt in bits 6:4 (7 = no wait), lgkmcnt in bits 11:8 (0 = wait for all).
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); }
-
-__device__ __forceinline__ void stage_barrier() {
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
 
 // sum of the values of lanes l and l^32 (both lanes get the same result)
 __device__ __forceinline__ float pair_sum(float v) {
@@ -1178,10 +1166,9 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void k_gemm(GemmParams p, int64_t s
                                                          CT* __restrict__ cout,
                                                          const RT* __restrict__ resid,
                                                          const float* __restrict__ gate) {
-  // the operand stages; the QKV epilogue at head_dim 128 needs a little more
-  constexpr int STAGES = 2 * 256 * ROWB + 3 * B_BYTES;
-  constexpr int EPI_LDS = EPI == EPI_QKV_HEADS_128 ? qkv_epi_lds_bytes(256, 128) : 0;
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[STAGES > EPI_LDS ? STAGES : EPI_LDS];
+  constexpr int STAGES = 2 * 256 * ROWB + 3 * B_BYTES;   // the operand stages, which the QKV epilogue uses again
+  static_assert(qkv_epi_lds_bytes(256, 128) <= STAGES && NWAVES * 64 * v_row(128) * 2 <= STAGES, "epilogue LDS");
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[STAGES];
   const int bx = (int)blockIdx.x;
   if (bx < first_small)
     gemm_tile<T, EPI, CT, RT, 128>(p, split, p.M, bx, smem, bias, cout, resid, gate);

@@ -165,13 +165,13 @@ def test_gemm_rows_independent_of_m():
 
 
 @pytest.mark.parametrize("M,N,K,epi", [
-    (16584, 3072, 12288, X.XEMA_EPI_GATED_RESIDUAL),   # 256-row tiles + a 128-row tail launch
-    (17776, 12288, 3072, X.XEMA_EPI_BIAS_GELU),        # 256-row tiles only
+    (16584, 3072, 12288, X.XEMA_EPI_GATED_RESIDUAL),   # 256-row tiles up to row 16384, then 128-row ones
+    (17776, 12288, 3072, X.XEMA_EPI_BIAS_GELU),        # up to row 17664
 ])
 def test_gemm_tile_heights_agree_at_full_size(M, N, K, epi):
-    """Large calls run 256-row tiles (and, where that fills the CUs better, a
-    second launch of 128-row tiles over the last rows); small calls run
-    128-row tiles.  Rows around the split and elsewhere are bit-identical to
+    """Large calls run 256-row tiles and, where that fills the CUs better,
+    128-row tiles over the last rows; small calls run 64 x 64, 64 x 128 or
+    128 x 96 ones.  Rows around the split and elsewhere are bit-identical to
     the same rows computed by a small call, and sampled rows match fp64."""
     g = torch.Generator(device=DEV).manual_seed(M + N)
     a = torch.randn(M, K, device=DEV, generator=g).half()
