@@ -115,7 +115,10 @@ int step_layout(const xema_block_cfg& c, const xema_request& r, int n_blocks, in
 
 // Modelled time of one block (all its groups and chunks), milliseconds: the
 // rounds of workgroups of each launch over the 256 CUs, a round costing one
-// workgroup's FLOPs at block_tflops / 256 per CU.
+// workgroup's FLOPs at block_tflops / 256 per CU.  The formula is xema_step.h's and
+// counts the largest tiles and workgroups only; the launchers take smaller ones
+// where those would leave CUs idle, so small chunks run faster than modelled (video
+// in 1000-token chunks 1.4 times the whole sequence's time, modelled 2.7).
 double block_ms(const xema_block_cfg& c, const xema_request& r, int64_t g, int64_t ch, double tflops) {
   const int64_t B = r.batch, L = seq_len(r), D = c.hidden, F = c.mlp_hidden, H = c.heads, d = c.head_dim;
   const int64_t qwg = d == 64 ? 512 : 256;  // queries per attention workgroup
